@@ -1,0 +1,401 @@
+"""Performance cases of the archive: the calls that a program serving a long-context model makes, through the
+public binding, at the sizes of the configurations, the tests and the benchmark.
+
+  evict      one decoding step: the position leaving the exact window is assigned on every stream (the streams
+             of a book together) and its symbols are appended to the archive
+  archive    prefill: residual-VQ assignment and span encode of a context's archived positions
+  restore    bulk decode of an archive back into symbols
+  lookup     random access to single tokens' symbols
+  rehydrate  random access and reconstruction of single tokens' K/V rows
+  index      per-position retrieval index of an archive
+  search     one suffix query over such an index
+  train      one Lloyd iteration of codebook training over all stages
+
+Streams are ordered (layer and K|V) row-major, then sequence, then head; the sequences of a batch share the
+books of their row and head.  Every second row holds keys, which have a few strong channels.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2607_07144_amd import fkv
+
+HISTORY = 4        # spans' worth of tokens in the archive before an eviction case's first step
+WINDOW = 64        # positions of the exact window that an eviction case walks through
+OUTLIERS, OUTLIER_SCALE = 4, 10.0
+
+
+def listed():
+    return [
+        # the smallest call: one decoding step of the GPT-2-shaped cache, a single sequence; launches count
+        dict(name="evict_gpt2", op="evict", rows=24, heads=12, batch=1, d=64, S=2, K=256, N=256),
+        # one decoding step of the 32-layer grouped-KV model, four sequences
+        dict(name="evict_long", op="evict", rows=64, heads=8, batch=4, d=128, S=3, K=256, N=256),
+        # prefill of a single 1024-token context (4 sink and 32 recent positions stay exact)
+        dict(name="archive_gpt2", op="archive", rows=24, heads=12, batch=1, tokens=988, d=64, S=2, K=256, N=256,
+             residual=False),
+        # a batch of 16 such contexts with a deeper quantizer for the keys ...
+        dict(name="archive_keys_b16", op="archive", rows=12, heads=12, batch=16, tokens=988, d=64, S=4, K=256, N=256,
+             residual=False),
+        # ... and a small-book one for the values
+        dict(name="archive_values_b16", op="archive", rows=12, heads=12, batch=16, tokens=988, d=64, S=2, K=64, N=64,
+             residual=False),
+        # the largest: 32,768-token contexts of the 32-layer grouped-KV model, four sequences
+        dict(name="archive_long", op="archive", rows=64, heads=8, batch=4, tokens=32732, d=128, S=3, K=256, N=256,
+             residual=False),
+        # restoring that whole archive
+        dict(name="restore_long", op="restore", streams=2048, tokens=32732, S=3, N=256, verify=False),
+        # 2^20 single tokens out of an archive of 144 streams x 131,072 tokens
+        dict(name="lookup_random", op="lookup", streams=144, tokens=131072, S=2, N=256, queries=1 << 20),
+        # 65,536 K/V rows out of the long-context archive
+        dict(name="rehydrate_long", op="rehydrate", rows=64, heads=8, batch=4, tokens=32732, d=128, S=3, K=256, N=256,
+             queries=1 << 16),
+        # retrieval over the archive of 144 streams: building the index, one query
+        dict(name="index_build", op="index", streams=144, tokens=131072, S=2, N=256),
+        dict(name="suffix_search", op="search", streams=144, tokens=131072, S=2, N=256, ell=6, verify=True),
+        # training the 512 books of the 32-layer model on one 32,768-token context
+        dict(name="train_long", op="train", rows=64, heads=8, batch=1, tokens=32732, d=128, S=3, K=256, N=256),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    """A case of the listed ones' ranges: head dimensions, depths and book sizes of the tests, streams and tokens
+    spread over their logarithm, odd ones among them."""
+    op = rng.choice(("evict", "archive", "archive", "restore", "lookup", "rehydrate", "index", "search", "train"))
+    rows, heads, batch = 2 * rng.randint(6, 32), rng.choice((4, 8, 12)), rng.choice((1, 1, 2, 3, 4, 8, 16))
+    d, S = rng.choice((64, 64, 80, 96, 128, 128)), rng.choice((2, 2, 3, 3, 4))
+    K = rng.choice((64, 100, 128, 256, 256, 256))
+    N = K if K in (64, 256) else 256
+    while rows * heads * batch > 2304:
+        rows -= 2
+    quantizer = dict(rows=rows, heads=heads, batch=batch, d=d, S=S, K=K, N=N)
+    if op == "evict":
+        return dict(op=op, **quantizer)
+    if op in ("archive", "train"):
+        most = 2048 * 32732 * (128 * 256 * 3) / (rows * heads * batch * d * K * S)
+        if op == "train":
+            most /= 4
+        tokens = _log(rng, 200, max(400, min(32732, most / 1.5)))
+        if op == "train":
+            return dict(op=op, tokens=tokens, **quantizer)
+        return dict(op=op, tokens=tokens, residual=tokens < 2000 and rng.random() < 0.25, **quantizer)
+    streams, tokens, N = _log(rng, 64, 2048), _log(rng, 500, 131072), rng.choice((16, 64, 256, 256, 256))
+    while streams * tokens > 1 << 24:
+        tokens = tokens // 2 + 1
+    if op == "restore":
+        return dict(op=op, streams=streams, tokens=tokens, S=S, N=N, verify=rng.random() < 0.3)
+    if op == "lookup":
+        return dict(op=op, streams=streams, tokens=tokens, S=S, N=N, queries=_log(rng, 1000, 1 << 20))
+    if op == "rehydrate":
+        tokens = _log(rng, 500, 32732)
+        return dict(op=op, tokens=tokens, queries=_log(rng, 1000, 1 << 18), **quantizer)
+    if op == "index":
+        return dict(op=op, streams=streams, tokens=tokens, S=S, N=N)
+    ell = rng.randint(5, 6) if N == 256 else rng.randint(7, 9) if N == 64 else rng.randint(11, 16)
+    return dict(op="search", streams=streams, tokens=tokens, S=S, N=N, ell=ell, verify=rng.random() < 0.7)
+
+
+# ---------------------------------------------------------------- inputs
+
+def _gen(seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(int(seed))
+    return g
+
+
+def _channel_scale(case, seed):
+    """[rows][heads][d]: strong channels of the keys (even rows)."""
+    rng = np.random.default_rng(int(seed))
+    scale = np.ones((case["rows"], case["heads"], case["d"]), np.float32)
+    for r in range(0, case["rows"], 2):
+        for h in range(case["heads"]):
+            scale[r, h, rng.choice(case["d"], OUTLIERS, replace=False)] = OUTLIER_SCALE
+    return torch.from_numpy(scale).cuda()
+
+
+def _books(case, seed):
+    """Books [rows * heads][S][K][d] whose codewords cover the channels' scales; each stage half the one before."""
+    rows, heads, d, S, K = (case[k] for k in ("rows", "heads", "d", "S", "K"))
+    b = torch.randn((rows, heads, S, K, d), generator=_gen(seed + 1000003), device="cuda")
+    b *= _channel_scale(case, seed)[:, :, None, None, :]
+    b *= (0.5 ** torch.arange(S, device="cuda", dtype=torch.float32))[None, None, :, None, None]
+    return b.to(torch.float16).view(rows * heads, S, K, d)
+
+
+def _vectors(case, tokens, seed):
+    """K/V head vectors [streams][tokens][d]."""
+    rows, heads, batch, d = (case[k] for k in ("rows", "heads", "batch", "d"))
+    gen, scale = _gen(seed), _channel_scale(case, seed)
+    x = torch.empty((rows, batch, heads, tokens, d), dtype=torch.float16, device="cuda")
+    for r in range(rows):
+        v = torch.randn((batch, heads, tokens, d), generator=gen, device="cuda")
+        x[r] = v.mul_(scale[r][None, :, None, :])
+    return x.view(rows * batch * heads, tokens, d)
+
+
+def _stream_book(case):
+    rows, heads, batch = (case[k] for k in ("rows", "heads", "batch"))
+    sb = np.arange(rows * heads, dtype=np.int32).reshape(rows, 1, heads)
+    return np.broadcast_to(sb, (rows, batch, heads)).reshape(-1).copy()
+
+
+def _symbols(streams, n_sym, N, seed):
+    """High-entropy index streams."""
+    return torch.randint(0, N, (streams, n_sym), generator=_gen(seed + 7), device="cuda", dtype=torch.uint8)
+
+
+def _queries(streams, tokens, n, seed):
+    g = _gen(seed + 11)
+    return (torch.randint(0, streams, (n,), generator=g, device="cuda", dtype=torch.int32),
+            torch.randint(0, tokens, (n,), generator=g, device="cuda", dtype=torch.int32))
+
+
+def _history(case):
+    return HISTORY * _span_length(case["N"])
+
+
+def _streams(case):
+    return case["streams"] if "streams" in case else case["rows"] * case["heads"] * case["batch"]
+
+
+def prepare(case, seed):
+    op = case["op"]
+    st = dict(case=case)
+    if op != "train":
+        st["codec"] = fkv.Codec(case["N"])
+        st["codec"].table()
+    if op in ("evict", "archive", "rehydrate", "train"):
+        sb = _stream_book(case)
+        st["stream_book"] = torch.from_numpy(sb).cuda()
+        st["books"] = _books(case, seed)
+    if op == "evict":
+        ns, S, hist = _streams(case), case["S"], _history(case)
+        st["x"] = _vectors(case, WINDOW, seed)
+        st["groups"] = torch.from_numpy(fkv.book_groups(sb)).cuda()
+        st["step"], st["symbols"] = 0, torch.zeros((ns, S), dtype=torch.uint8, device="cuda")
+        st["points"] = torch.zeros((ns, st["codec"].n_spans((hist + WINDOW) * S), 2), dtype=torch.float64, device="cuda")
+        past = fkv.fkv_cgr_encode_spans(st["codec"], _symbols(ns, hist * S, min(case["N"], case["K"]), seed))
+        st["points"][:, :past.shape[1]] = past
+    elif op == "archive":
+        st["x"] = _vectors(case, case["tokens"], seed)
+    elif op == "train":
+        st["x"] = _vectors(case, case["tokens"], seed)
+        nb, S, K, d = st["books"].shape
+        st["symbols"] = torch.zeros((_streams(case), case["tokens"] * S), dtype=torch.uint8, device="cuda")
+        st["sums"] = torch.zeros((nb, K, d), dtype=torch.int64, device="cuda")
+        st["counts"] = torch.zeros((nb, K), dtype=torch.int32, device="cuda")
+    else:
+        ns, n_sym = _streams(case), case["tokens"] * case["S"]
+        sym = _symbols(ns, n_sym, min(case["N"], case.get("K", 256)), seed)
+        if op == "index":
+            st["symbols"] = sym
+        elif op == "search":
+            st["index"] = fkv.fkv_trajectory(st["codec"], sym)
+            s, t = _place(case, seed)
+            st["query"] = sym[s, t:t + case["ell"]].contiguous()
+            st["hits"] = torch.zeros((1024, 2), dtype=torch.int32, device="cuda")
+        else:
+            st["points"] = fkv.fkv_cgr_encode_spans(st["codec"], sym)
+            if op != "restore":
+                st["q_stream"], st["q_token"] = _queries(ns, case["tokens"], case["queries"], seed)
+    return st
+
+
+def _place(case, seed):
+    """Where a search case's query is taken from."""
+    rng = np.random.default_rng(int(seed) + 13)
+    return int(rng.integers(_streams(case))), int(rng.integers(case["tokens"] * case["S"] - case["ell"]))
+
+
+# ---------------------------------------------------------------- one pass
+
+def run(st):
+    case = st["case"]
+    op, S = case["op"], case.get("S")
+    if op == "evict":
+        t = st["step"]
+        st["step"] = (t + 1) % WINDOW
+        sym, _ = fkv.fkv_rvq_assign_groups(st["x"], st["books"], st["stream_book"], st["groups"], t, t + 1,
+                                           symbols=st["symbols"])
+        pts = fkv.fkv_cgr_append(st["codec"], st["points"], (_history(case) + t) * S, sym)
+        return {"symbols": sym, "points": pts}
+    if op == "archive":
+        sym, pts, res = fkv.fkv_rvq_assign_encode(st["codec"], st["x"], st["books"], st["stream_book"], 0,
+                                                  case["tokens"], want_residual=case["residual"])
+        return {"symbols": sym, "points": pts, "residual": res} if case["residual"] else {"symbols": sym, "points": pts}
+    if op == "restore":
+        n_failed = torch.zeros(1, dtype=torch.int32, device="cuda")
+        sym = fkv.fkv_cgr_decode_spans(st["codec"], st["points"], case["tokens"] * S, n_failed=n_failed,
+                                       verify=case["verify"])
+        return {"symbols": sym, "failed": n_failed}
+    if op == "lookup":
+        return {"symbols": fkv.fkv_span_lookup(st["codec"], st["points"], case["tokens"] * S, S, st["q_stream"],
+                                               st["q_token"])}
+    if op == "rehydrate":
+        return {"rows": fkv.fkv_rehydrate(st["codec"], st["points"], case["tokens"] * S, S, st["books"],
+                                          st["stream_book"], st["q_stream"], st["q_token"])}
+    if op == "index":
+        return {"index": fkv.fkv_trajectory(st["codec"], st["symbols"])}
+    if op == "search":
+        hits, n_hits, n_cand = fkv.fkv_suffix_search(st["codec"], st["index"], st["query"], verify=case["verify"],
+                                                     max_hits=st["hits"].shape[0], hits=st["hits"])
+        return {"hits": hits, "n_hits": n_hits, "n_candidates": n_cand}
+    for stage in range(S):
+        fkv.fkv_rvq_assign(st["x"], st["books"], st["stream_book"], 0, case["tokens"], symbols=st["symbols"],
+                           n_stages=stage + 1)
+        fkv.fkv_kmeans_step(st["x"], st["books"], st["stream_book"], 0, case["tokens"], st["symbols"], stage,
+                            sums=st["sums"], counts=st["counts"])
+    return {"books": st["books"], "counts": st["counts"]}
+
+
+# ---------------------------------------------------------------- floor and tolerance
+
+def work(case):
+    op, ns, S, N = case["op"], _streams(case), case["S"], case["N"]
+    L = _span_length(N)
+    book = case["rows"] * case["heads"] * case["S"] * case["K"] * case["d"] * 2 if "rows" in case else 0
+    if op == "evict":
+        d, K = case["d"], case["K"]
+        return {"bytes": ns * (2 * d + S + 32) + book, "flops": 2 * ns * S * K * d}
+    if op == "archive":
+        v, d, K = ns * case["tokens"], case["d"], case["K"]
+        spans = ns * (-(-case["tokens"] * S // L))
+        return {"bytes": v * (2 * d + S + (4 * d if case["residual"] else 0)) + 16 * spans + book,
+                "flops": 2 * v * S * K * d}
+    if op == "train":
+        # the vectors, and the symbols and books, once each; each stage needs its scores once
+        v, d, K = ns * case["tokens"], case["d"], case["K"]
+        return {"bytes": v * (2 * d + S) + 2 * book, "flops": 2 * v * S * K * d}
+    n = ns * case["tokens"] * S
+    spans = ns * (-(-case["tokens"] * S // L))
+    if op == "restore":
+        return {"bytes": n + 16 * spans, "flops": 4 * n}
+    if op == "lookup":
+        return {"bytes": case["queries"] * (8 + S + 16 * (1 + (S - 1) / L)), "flops": 4 * L * case["queries"]}
+    if op == "rehydrate":
+        q, d = case["queries"], case["d"]
+        return {"bytes": q * (8 + 16 * (1 + (S - 1) / L) + 2 * d) + min(book, q * S * d * 2), "flops": q * S * d}
+    if op == "index":
+        return {"bytes": 17 * n, "flops": 6 * n * L}
+    return {"bytes": 16 * n, "flops": 6 * n}
+
+
+def tolerance(case):
+    # Every output is a stored code: bytes, points that are compared bit for bit when an archive is verified,
+    # integer sums and means rounded once.  Two passes and the oracle agree to the last bit, and a point whose
+    # span has one other symbol is another point altogether, so nothing looser than equality says anything.
+    return "exact"
+
+
+# ---------------------------------------------------------------- the same in 64 bits, in plain torch
+
+def _ratio(N):
+    s = math.sin(math.pi / N)
+    m = max(math.sin((2 * j + 1) * math.pi / N) for j in range(N))
+    return 0.98 * (s / (s + m))
+
+
+def _span_length(N):
+    return int(math.floor(44 / math.log2(1 / _ratio(N))))
+
+
+def _vertices(N):
+    a = 2 * math.pi * torch.arange(N, dtype=torch.float64) / N
+    return torch.stack((torch.cos(a), torch.sin(a)), dim=1).cuda()
+
+
+def _encode(sym, N):
+    ns, n = sym.shape
+    L, r, V = _span_length(N), _ratio(N), _vertices(N)
+    spans = -(-n // L)
+    p = torch.zeros((ns, spans, 2), dtype=torch.float64, device="cuda")
+    for k in range(L):
+        m = (n - k + L - 1) // L if n > k else 0   # spans with a k-th symbol
+        if m:
+            v = V[sym[:, k::L].long()]
+            p[:, :m] = v + r * (p[:, :m] - v)
+    return p
+
+
+def _assign(x, books, sb, residual=False):
+    """Greedy residual quantization of x [streams][tokens][d], a stream at a time: symbols, and the residual."""
+    ns, T, d = x.shape
+    S = books.shape[1]
+    sym = torch.empty((ns, T, S), dtype=torch.uint8, device="cuda")
+    res = torch.empty((ns, T, d), dtype=torch.float64, device="cuda") if residual else None
+    for s in range(ns):
+        book = books[int(sb[s])].double()
+        r = x[s].double()
+        for k in range(S):
+            c = book[k]
+            i = ((c * c).sum(1) / 2 - r @ c.t().contiguous()).argmin(1)
+            sym[s, :, k] = i
+            r = r - c[i]
+        if residual:
+            res[s] = r
+    return sym.view(ns, T * S), res
+
+
+def exact(case, seed):
+    op, S, N = case["op"], case["S"], case["N"]
+    if op in ("evict", "archive", "train"):
+        books, sb = _books(case, seed), _stream_book(case)
+    if op == "evict":
+        ns, hist = _streams(case), _history(case)
+        L = _span_length(N)
+        sym, _ = _assign(_vectors(case, WINDOW, seed)[:, :1].contiguous(), books, sb)
+        pts = torch.zeros((ns, -(-(hist + WINDOW) * S // L), 2), dtype=torch.float64, device="cuda")
+        past = _encode(torch.cat((_symbols(ns, hist * S, min(N, case["K"]), seed), sym), dim=1), N)
+        pts[:, :past.shape[1]] = past
+        return {"symbols": sym, "points": pts}
+    if op == "archive":
+        sym, res = _assign(_vectors(case, case["tokens"], seed), books, sb, case["residual"])
+        out = {"symbols": sym, "points": _encode(sym, N)}
+        if case["residual"]:
+            out["residual"] = res
+        return out
+    if op == "train":
+        x, ns = _vectors(case, case["tokens"], seed), _streams(case)
+        new = books.double()
+        members = np.argsort(sb, kind="stable").reshape(books.shape[0], -1)
+        for b in range(books.shape[0]):
+            v = x[torch.from_numpy(members[b]).cuda()].view(-1, case["d"]).double()
+            for stage in range(S):
+                r = v
+                for k in range(stage + 1):
+                    c = new[b, k]
+                    i = ((c * c).sum(1) / 2 - r @ c.t().contiguous()).argmin(1)
+                    if k < stage:
+                        r = r - c[i]
+                n = torch.zeros(case["K"], dtype=torch.float64, device="cuda").index_add_(0, i, torch.ones_like(r[:, 0]))
+                s = torch.zeros_like(new[b, stage]).index_add_(0, i, r)
+                mean = torch.where(n[:, None] > 0, s / n.clamp(min=1)[:, None], new[b, stage])
+                new[b, stage] = mean.to(torch.float16).double()
+        return {"books": new, "counts": None}
+    sym = _symbols(_streams(case), case["tokens"] * S, min(N, case.get("K", 256)), seed)
+    if op == "restore":
+        return {"symbols": sym, "failed": torch.zeros(1, dtype=torch.int32)}
+    if op == "index":
+        L, r, V = _span_length(N), _ratio(N), _vertices(N)
+        p = torch.zeros((*sym.shape, 2), dtype=torch.float64, device="cuda")
+        for back in range(L - 1, -1, -1):   # the symbol `back` positions before each point's own
+            if sym.shape[1] > back:
+                v = V[sym[:, :sym.shape[1] - back].long()]
+                p[:, back:] = v + r * (p[:, back:] - v)
+        return {"index": p}
+    if op == "search":
+        return None   # positions and counts, all whole numbers
+    qs, qt = _queries(_streams(case), case["tokens"], case["queries"], seed)
+    got = sym.view(_streams(case), case["tokens"], S)[qs.long(), qt.long()]
+    if op == "lookup":
+        return {"symbols": got}
+    books, sb = _books(case, seed), torch.from_numpy(_stream_book(case)).cuda()
+    rows = torch.zeros((case["queries"], case["d"]), dtype=torch.float64, device="cuda")
+    for k in range(S):
+        rows += books[sb[qs.long()].long(), k, got[:, k].long()].double()
+    return {"rows": rows}
