@@ -177,7 +177,8 @@ def prepare(case, seed):
         ns, S, hist = _streams(case), case["S"], _history(case)
         st["x"] = _vectors(case, WINDOW, seed)
         st["groups"] = torch.from_numpy(fkv.book_groups(sb)).cuda()
-        st["step"], st["symbols"] = 0, torch.zeros((ns, S), dtype=torch.uint8, device="cuda")
+        st["step"], st["n_sym"] = 0, hist * S
+        st["symbols"] = torch.zeros((ns, S), dtype=torch.uint8, device="cuda")
         st["points"] = torch.zeros((ns, st["codec"].n_spans((hist + WINDOW) * S), 2), dtype=torch.float64, device="cuda")
         past = fkv.fkv_cgr_encode_spans(st["codec"], _symbols(ns, hist * S, min(case["N"], case["K"]), seed))
         st["points"][:, :past.shape[1]] = past
@@ -222,7 +223,7 @@ def run(st):
         st["step"] = (t + 1) % WINDOW
         sym, _ = fkv.fkv_rvq_assign_groups(st["x"], st["books"], st["stream_book"], st["groups"], t, t + 1,
                                            symbols=st["symbols"])
-        pts = fkv.fkv_cgr_append(st["codec"], st["points"], (_history(case) + t) * S, sym)
+        pts = fkv.fkv_cgr_append(st["codec"], st["points"], st["n_sym"] + t * S, sym)
         return {"symbols": sym, "points": pts}
     if op == "archive":
         sym, pts, res = fkv.fkv_rvq_assign_encode(st["codec"], st["x"], st["books"], st["stream_book"], 0,
