@@ -16,6 +16,8 @@
 // points equal a bulk encode of the whole stream bit for bit.
 #include "cgr_device.h"
 
+#include <type_traits>
+
 namespace fkv {
 namespace {
 
@@ -190,50 +192,76 @@ __global__ __launch_bounds__(kBlock) void append_kernel(double2* __restrict__ pt
 // candidate, kept when decoding ell symbols backward from it reproduces the
 // query.  The scan streams the index once (16 bytes per position).
 
-// WC > 0: the window length is WC, known at compile time, and full windows
-// are walked fully unrolled (the first WC - 1 positions of a stream, with
-// shorter windows, take the loop).
-template <int WC>
-__global__ __launch_bounds__(kBlock) void trajectory_kernel(const uint8_t* __restrict__ sym,
-                                                             double2* __restrict__ traj,
-                                                             const uint8_t* __restrict__ gtab, CodecArgs cd,
-                                                             int64_t n_sym, int W, int64_t tiles_per_stream,
-                                                             int64_t n_tiles)
+// A block takes one tile of U x 256 positions of a stream, in position order
+// over the grid: the blocks in flight then write one moving window of the
+// index.  (A persistent grid striding over 256-position tiles drifts apart and
+// writes at 4.5 TB/s whatever it computes; a kernel that only writes, one tile
+// per block, reaches 6.2-6.8 TB/s.)  At N = 256 it runs at 5.8 TB/s: beside the
+// writes, a wave needs six random 16-byte LDS reads per 64 positions.
+template <int WC, int U>
+__global__ __launch_bounds__(kBlock, 8) void trajectory_kernel(const uint8_t* __restrict__ sym,
+                                                                double2* __restrict__ traj,
+                                                                const uint8_t* __restrict__ gtab, CodecArgs cd,
+                                                                int64_t n_sym, int W, int64_t tiles_per_stream,
+                                                                int64_t n_tiles)
 {
+    constexpr int TILE = U * kBlock;
     extern __shared__ __align__(16) uint8_t lds[];
-    const int N = cd.N;
+    const int N = cd.N, tid = threadIdx.x;
     double2* V = (double2*)lds;
     uint8_t* tile = lds + 256 * sizeof(double2);
-    V[threadIdx.x] = (int)threadIdx.x < N ? ((const double2*)(gtab + table_off_V(N)))[threadIdx.x]
-                                          : make_double2(NAN, NAN);
-    TileWalk w;
-    w.init(blockIdx.x, gridDim.x, tiles_per_stream);
-    for (int64_t tl = blockIdx.x; tl < n_tiles; tl += gridDim.x, w.next()) {
-        const int64_t s = w.s;
-        const int64_t k0 = w.j * kBlock;
+    const double2 vreg = tid < N ? ((const double2*)(gtab + table_off_V(N)))[tid] : make_double2(NAN, NAN);
+    bool staged = false;
+    for (int64_t tl = blockIdx.x; tl < n_tiles; tl += gridDim.x) {
+        // a 64-bit division is emulated
+        const int64_t s = n_tiles <= 0x7fffffff ? (int64_t)((uint32_t)tl / (uint32_t)tiles_per_stream) : tl / tiles_per_stream;
+        const int64_t k0 = (tl - s * tiles_per_stream) * TILE;
         const int64_t a0 = max((int64_t)0, k0 - W + 1);
-        const int64_t k1 = min(n_sym, k0 + kBlock);
-        const int64_t g0 = s * n_sym + a0, g1 = s * n_sym + k1;
-        __syncthreads();   // previous tile consumed
+        const int nk = (int)min((int64_t)TILE, n_sym - k0);
+        const int h = (int)(k0 - a0);   // symbols of history before the tile
+        const int64_t g0 = s * n_sym + a0, g1 = s * n_sym + k0 + nk;
+        if (staged) __syncthreads();   // previous tile consumed
         bytes_to_lds(sym, g0, g1, tile);
+        if (!staged) V[tid] = vreg;
+        staged = true;
         __syncthreads();
-        const int64_t k = k0 + threadIdx.x;
-        if (k < k1) {
-            const int Wn = WC > 0 ? WC : W;
-            const int64_t a = max((int64_t)0, k - Wn + 1);
-            const uint8_t* my = tile + (g0 & 3) + (int)(a - a0);
-            const int len = (int)(k - a) + 1;
+        const int base = (int)(g0 & 3) + h;   // LDS offset of position k0's own symbol
+        double2* out = traj + s * n_sym + k0;
+        // the full window ending at k0 + k: its bytes from the aligned LDS
+        // dwords that cover them, then the walk
+        auto walk = [&](int k) {
+            constexpr int NE = WC > 0 ? (WC + 3) / 4 : 1;
+            const int off = base + k + 1 - WC;
+            const uint32_t* t32 = (const uint32_t*)tile + (off >> 2);
+            uint32_t dw[NE + 1], e[NE];
+#pragma unroll
+            for (int q = 0; q <= NE; ++q) dw[q] = t32[q];
+#pragma unroll
+            for (int q = 0; q < NE; ++q) e[q] = __builtin_amdgcn_alignbyte(dw[q + 1], dw[q], off);
+            double2 v[WC > 0 ? WC : 1];
+#pragma unroll
+            for (int j = 0; j < WC; ++j) v[j] = V[(e[j >> 2] >> (8 * (j & 3))) & 0xFF];
             double px = 0.0, py = 0.0;
-            if (WC > 0 && len == WC) {
-                double2 v[WC > 0 ? WC : 1];
 #pragma unroll
-                for (int u = 0; u < WC; ++u) v[u] = V[my[u]];
+            for (int j = 0; j < WC; ++j) encode_step(px, py, v[j], cd.r);
+            store_point_stream(out + k, px, py);
+        };
+        if (WC > 0 && nk == TILE && h == WC - 1) {
+            // whole tile, every window full: no predicate, so the walks interleave
 #pragma unroll
-                for (int u = 0; u < WC; ++u) encode_step(px, py, v[u], cd.r);
-            } else {
+            for (int u = 0; u < U; ++u) walk(u * kBlock + tid);
+        } else {
+            for (int k = tid; k < nk; k += kBlock) {
+                if (WC > 0 && h + k + 1 >= WC) {
+                    walk(k);
+                    continue;
+                }
+                const int len = min(WC > 0 ? WC : W, h + k + 1);
+                const uint8_t* my = tile + base + k + 1 - len;
+                double px = 0.0, py = 0.0;
                 for (int j = 0; j < len; ++j) encode_step(px, py, V[my[j]], cd.r);
+                store_point_stream(out + k, px, py);
             }
-            store_point_stream(traj + s * n_sym + k, px, py);
         }
     }
 }
@@ -383,22 +411,36 @@ extern "C" int fkv_trajectory(const fkv_codec* c, const void* dev_table, const u
     if (n_streams == 0 || n_sym == 0) return FKV_OK;
     if (!symbols || !traj || !aligned(symbols, 4) || !aligned(traj, 16) || !aligned(dev_table, 16))
         return FKV_ERR_INVALID_ARG;
-    const int64_t tps = (n_sym + kBlock - 1) / kBlock;
-    const int64_t n_tiles = tps * n_streams;
-    const size_t shm = 256 * 16 + (size_t)kBlock + 64 + 16;
     // the codec's own span length L is the usual window: 6, 9 and 16 for N = 256, 64 and 16
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks_for(n_tiles)), dim3(kBlock), shm, (hipStream_t)stream, symbols,
-                           (double2*)traj, (const uint8_t*)dev_table, codec_args(c), n_sym, W, tps, n_tiles);
+    auto go = [&](auto kern, int tile) {
+        const int64_t tps = (n_sym + tile - 1) / tile;
+        const int64_t n_tiles = tps * n_streams;
+        const size_t shm = 256 * 16 + (size_t)tile + 64 + 16;
+        hipLaunchKernelGGL(kern, dim3((unsigned)min(n_tiles, kMaxTileBlocks)), dim3(kBlock), shm, (hipStream_t)stream,
+                           symbols, (double2*)traj, (const uint8_t*)dev_table, codec_args(c), n_sym, W, tps, n_tiles);
     };
-    if (W == 6)
-        go(trajectory_kernel<6>);
-    else if (W == 9)
-        go(trajectory_kernel<9>);
-    else if (W == 16)
-        go(trajectory_kernel<16>);
+    auto pick = [&](auto u) {
+        constexpr int U = decltype(u)::value;
+        if (W == 6)
+            go(trajectory_kernel<6, U>, U * kBlock);
+        else if (W == 9)
+            go(trajectory_kernel<9, U>, U * kBlock);
+        else if (W == 16)
+            go(trajectory_kernel<16, U>, U * kBlock);
+        else
+            go(trajectory_kernel<0, U>, U * kBlock);
+    };
+    // Tiles of 2048 positions once they give every compute unit two blocks,
+    // else of 256, so that a small index still spreads over the chip (kernel
+    // time differs by less than a launch there).  Measured with 256- and
+    // 2048-position tiles: 37.7 M positions 166 and 110 us (the persistent
+    // 256-position form this replaced 135 us: 4.7 -> 5.8 TB/s), 4.0 M 21.5 and
+    // 17.8 us, 0.9 M 10.9 and 11.2 us.
+    const bool big = n_streams * ((n_sym + 8 * kBlock - 1) / (8 * kBlock)) >= 512;
+    if (big)
+        pick(std::integral_constant<int, 8>{});
     else
-        go(trajectory_kernel<0>);
+        pick(std::integral_constant<int, 1>{});
     return launch_status();
 }
 

@@ -47,6 +47,23 @@ def test_trajectory_short_streams(fkv, orc, n_sym, W):
     assert np.array_equal(host(tr).view(np.uint64), want.view(np.uint64))
 
 
+@pytest.mark.parametrize("ns,n_sym,N,W", [(512, 37, 256, 6), (512, 3, 256, 6), (257, 2049, 256, 6), (171, 4100, 64, 9),
+                                          (256, 2051, 16, 16), (130, 6145, 256, 7), (512, 2047, 3, 64)])
+def test_trajectory_large_tiles(fkv, orc, ns, n_sym, N, W):
+    """Indexes of at least 512 tiles of 2048 positions: whole tiles, one-position remainders, streams shorter
+    than a tile or the window, odd stream lengths (every byte alignment), symbols outside the alphabet."""
+    rng = np.random.default_rng(ns + n_sym)
+    sym = rng.integers(0, N, (ns, n_sym), dtype=np.uint8)
+    want = orc.trajectory(orc.Codec(N), sym, W)
+    if N < 256:
+        sym[1, n_sym // 2] = N          # NaN points while it is in the window
+        want[1, n_sym // 2:n_sym // 2 + W] = np.nan
+    tr = host(fkv.fkv_trajectory(fkv.Codec(N), torch.from_numpy(sym).cuda(), W))
+    bad = np.isnan(want)
+    assert np.array_equal(np.isnan(tr), bad)
+    assert np.array_equal(tr.view(np.uint64)[~bad], want.view(np.uint64)[~bad])
+
+
 @pytest.mark.parametrize("N", [16, 64, 256])
 def test_suffix_search_matches_oracle(fkv, orc, N):
     rng = np.random.default_rng(7 * N)
