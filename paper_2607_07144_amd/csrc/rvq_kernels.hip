@@ -117,8 +117,25 @@ __device__ __forceinline__ void book_to_lds_async(const _Float16* __restrict__ C
     }
 }
 
-// Bias-step A chunk of every row of NB buffers: (-||c||^2/2 as hi + mid + lo
-// fp16 parts, 1, 2^14, 0, 0, 0), written into the row's last slot.  All rows'
+// Bias-step A chunk of a codeword with squared norm `acc`: (-||c||^2/2 as hi +
+// mid + lo fp16 parts, 1, 2^14, 0, 0, 0).
+__device__ __forceinline__ half8 bias_row(float acc)
+{
+    const float n = -0.5f * acc;
+    const _Float16 hi = (_Float16)n;
+    const float rem = n - (float)hi;
+    const _Float16 mid = (_Float16)rem;
+    const _Float16 lo = (_Float16)(rem - (float)mid);
+    half8 a = (half8)(_Float16)0;
+    a[0] = hi;
+    a[1] = mid;
+    a[2] = lo;
+    a[3] = (_Float16)1.0f;
+    a[4] = (_Float16)kBiasHiScale;
+    return a;
+}
+
+// The bias-step A chunk of every row of NB buffers, written into the row's last slot.  All rows'
 // LDS reads are issued before any norm is formed, so their latencies overlap.
 template <int D, int NB>
 __device__ __forceinline__ void book_bias_rows(uint8_t* buf0, uint8_t* buf1, int Kp)
@@ -142,18 +159,7 @@ __device__ __forceinline__ void book_bias_rows(uint8_t* buf0, uint8_t* buf1, int
                     acc = __builtin_amdgcn_fdot2(h, h, acc, false);
                 }
             }
-            const float n = -0.5f * acc;
-            const _Float16 hi = (_Float16)n;
-            const float rem = n - (float)hi;
-            const _Float16 mid = (_Float16)rem;
-            const _Float16 lo = (_Float16)(rem - (float)mid);
-            half8 a = (half8)(_Float16)0;
-            a[0] = hi;
-            a[1] = mid;
-            a[2] = lo;
-            a[3] = (_Float16)1.0f;
-            a[4] = (_Float16)kBiasHiScale;
-            *(half8*)(row[b] + NCH * 16) = a;
+            *(half8*)(row[b] + NCH * 16) = bias_row(acc);
         }
     }
 }
@@ -878,6 +884,239 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, kSmallBlocks) void rvq_small_kerne
     }
 }
 
+// ---- few tokens per book: at most 32 per work item --------------------------
+// A decoding step's eviction assigns one token per stream (per group of streams
+// sharing a book: a few).  Its work is reading the books once (100 MB for 512
+// books of 3 x 256 x 128), so nothing is staged: wave w owns codeword tile w of
+// every stage, loads its A fragments straight from global memory into
+// registers, forms the tile's norms there, and the block's waves meet only to
+// compare their best codewords and to pass the chosen rows on.  The token rows
+// and their residual parts live in LDS.  Two 8-wave blocks (three at d <= 64)
+// fit a compute unit, so their loads and scans overlap; the staged form runs
+// one block per compute unit, which waits on three 64 KB copies for the scan of
+// a single wave.  512 books of 3 x 256 x 128, four tokens each: 36.0 -> 21.4 us
+// (2.8 -> 4.7 TB/s of books); 576 of 4 x 256 x 64: 39.5 -> 23 us.  What bounds it
+// now is the L1 rate of the fragment loads (32-byte pieces of 32 rows per
+// instruction).  Slower: the next stage's fragments in registers too (spills, or
+// one block per compute unit: 29-60 us), its lines touched ahead (34 us).
+// Scores, keys, biases and residual splits are rvq_assign_kernel's, operation
+// for operation, and the winner is the lowest (score key, codeword) there too.
+constexpr int kFewTokens = 32;
+
+template <int D>
+struct FewLds {
+    static constexpr int PITCH = (D / 8 + 1) * 16;   // bytes per token row: odd number of 16-byte chunks
+    half8 pad_;                                      // (alignment)
+    uint8_t hi[kFewTokens * PITCH], lo[kFewTokens * PITCH], chosen[kFewTokens * PITCH];
+    uint64_t best[8][kFewTokens];                    // each wave's best (score key, codeword) per token
+};
+
+template <int D, bool GRP>
+__global__ __launch_bounds__(512, D <= 64 ? 6 : D <= 128 ? 4 : 2) void rvq_few_kernel(
+    const _Float16* __restrict__ x, const _Float16* __restrict__ books, const int32_t* __restrict__ stream_book,
+    uint8_t* __restrict__ symbols, float* __restrict__ residual, uint32_t* __restrict__ n_bad, int64_t T,
+    int64_t t_begin, int64_t Ta, int S, int NS, int K, int n_books, const int32_t* __restrict__ groups, int G,
+    int64_t n_streams, int64_t n_items)
+{
+    constexpr int KS = D / 16, NCH = D / 8, PITCH = FewLds<D>::PITCH;
+        __shared__ FewLds<D> l;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, hh = lane >> 5, n_waves = blockDim.x >> 6;
+    const int nt = (int)(GRP ? G * Ta : Ta);   // <= kFewTokens
+    for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+        // token i of the item: member stream and position, output row
+        auto token = [&](int i, int64_t& xr, int64_t& orow) {
+            const int e = GRP ? i / (int)Ta : 0, t = GRP ? i - e * (int)Ta : i;
+            const int64_t m = GRP ? (int64_t)groups[item * G + e] : item;
+            const bool in = m >= 0 && m < n_streams;
+            xr = (in ? m : 0) * T + t_begin + t;
+            orow = in ? m * Ta + t : -1;
+        };
+        int b;
+        if constexpr (GRP) {
+            const int32_t m0 = groups[item * G];
+            const int gb = (m0 >= 0 && m0 < n_streams) ? stream_book[m0] : -1;
+            int bad = gb < 0 || gb >= n_books;
+            if (tid < G) {
+                const int32_t m = groups[item * G + tid];
+                bad |= m < 0 || m >= n_streams || stream_book[m] != gb;
+            }
+            b = __syncthreads_or(bad) ? -1 : gb;
+        } else {
+            b = stream_book[item];
+            if (b < 0 || b >= n_books) b = -1;
+            __syncthreads();   // the previous item's rows are consumed
+        }
+        if (b < 0) {
+            for (int i = tid; i < nt * S; i += blockDim.x) {
+                int64_t xr, orow;
+                token(i / S, xr, orow);
+                if (orow >= 0) symbols[orow * S + i % S] = 0xFF;
+            }
+            if (residual)
+                for (int i = tid; i < nt * D; i += blockDim.x) {
+                    int64_t xr, orow;
+                    token(i / D, xr, orow);
+                    if (orow >= 0) residual[orow * D + i % D] = NAN;
+                }
+            if (tid == 0 && n_bad) atomicAdd(n_bad, 1u);
+            continue;
+        }
+        const _Float16* bk = books + (int64_t)b * S * K * D;
+
+        // rows >= K read row K - 1: they tie with it and give its index
+        const _Float16* my_row = bk + (int64_t)min(32 * wave + col, K - 1) * D + 8 * hh;
+        half8 f[KS];
+        auto load_frags = [&](int st) {
+            const _Float16* p = my_row + (int64_t)st * K * D;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) f[ks] = *(const half8*)(p + 16 * ks);
+        };
+        load_frags(0);
+        for (int i = tid; i < kFewTokens * NCH; i += blockDim.x) {
+            const int t = i / NCH, c = i - t * NCH;
+            half8 v = (half8)(_Float16)0;
+            if (t < nt) {
+                int64_t xr, orow;
+                token(t, xr, orow);
+                v = *(const half8*)(x + xr * D + 8 * c);
+            }
+            *(half8*)(l.hi + t * PITCH + 16 * c) = v;
+            *(half8*)(l.lo + t * PITCH + 16 * c) = (half8)(_Float16)0;
+        }
+        // this lane's token: member stream and position
+        const int my_e = GRP ? min(col, nt - 1) / (int)Ta : 0, my_t = min(col, nt - 1) - my_e * (int)Ta;
+        const int64_t my_m = GRP ? (int64_t)groups[item * G + my_e] : item;
+        __syncthreads();
+
+        const uint8_t* hi_l = l.hi + col * PITCH + 16 * hh;
+        const uint8_t* lo_l = l.lo + col * PITCH + 16 * hh;
+        float bias;
+        {
+            float n2 = 0.0f;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const half8 v = *(const half8*)(hi_l + 32 * ks);
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) {
+                    const half2 h = {v[e], v[e + 1]};
+                    n2 = __builtin_amdgcn_fdot2(h, h, n2, false);
+                }
+            }
+            n2 += __uint_as_float(lane_xor32(__float_as_uint(n2), hh));
+            bias = 0.5f * n2 * (1.0f + 0x1p-10f);
+        }
+
+        for (int st = 0; st < NS; ++st) {
+            const bool last = st + 1 == NS;
+            // bias-step fragment: the row's norm summed chunk by chunk in order
+            // (each half-wave holds every second chunk; the swap gives both
+            // halves the even and the odd one)
+            half8 fb = (half8)(_Float16)0;
+            {
+                typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+                float acc = 0.0f;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    const u32x4 own = __builtin_bit_cast(u32x4, f[ks]);
+                    uint32_t odd[4];
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const auto r = __builtin_amdgcn_permlane32_swap(own[w], own[w], false, false);
+                        const uint32_t even = r[0];
+                        odd[w] = r[1];
+                        acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2, even), __builtin_bit_cast(half2, even),
+                                                     acc, false);
+                    }
+#pragma unroll
+                    for (int w = 0; w < 4; ++w)
+                        acc = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2, odd[w]), __builtin_bit_cast(half2, odd[w]),
+                                                     acc, false);
+                }
+                const half8 a = bias_row(acc);
+                if (hh == 0) fb = a;
+            }
+            const half8 bz = bias_column(bias, hh);
+            floatx16 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb, bz, (floatx16)0.0f, 0, 0, 0);
+            if (st == 0) {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[ks], *(const half8*)(hi_l + 32 * ks), acc, 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[ks], *(const half8*)(hi_l + 32 * ks), acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f[ks], *(const half8*)(lo_l + 32 * ks), acc, 0, 0, 0);
+                }
+            }
+            const uint32_t key = tile_min_key<0>(acc);
+            const int li = (int)(key & 31u);
+            uint32_t cw = min((uint32_t)(32 * wave + 8 * (li >> 2) + 4 * hh + (li & 3)), (uint32_t)K - 1);
+            uint32_t val = key & ~31u;
+            {
+                const uint32_t oval = lane_xor32(val, hh), ocw = lane_xor32(cw, hh);
+                if (oval < val || (oval == val && ocw < cw)) {
+                    val = oval;
+                    cw = ocw;
+                }
+            }
+            if (hh == 0) l.best[wave][col] = (uint64_t)val << 32 | cw;
+            __syncthreads();
+            uint64_t best = l.best[0][col];
+            for (int w = 1; w < n_waves; ++w) best = min(best, l.best[w][col]);
+            cw = (uint32_t)best;
+            bias = -__uint_as_float((uint32_t)(best >> 32)) * (1.0f + 0x1p-10f);
+            if (wave == 0 && hh == 0 && col < nt) symbols[(my_m * Ta + my_t) * S + st] = (uint8_t)cw;
+            if (last && !residual) break;
+            // the wave that owns a token's chosen row passes it on
+            for (uint64_t mine = __ballot(lane < nt && (int)(cw >> 5) == wave); mine; mine &= mine - 1) {
+                const int t = __builtin_ctzll(mine);
+                if (col == (__builtin_amdgcn_readlane((int)cw, t) & 31)) {
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) *(half8*)(l.chosen + t * PITCH + 16 * hh + 32 * ks) = f[ks];
+                }
+            }
+            if (!last) load_frags(st + 1);
+            __syncthreads();
+            for (int i = tid; i < nt * NCH; i += blockDim.x) {
+                const int t = i / NCH, c = i - t * NCH;
+                const half8 cv = *(const half8*)(l.chosen + t * PITCH + 16 * c);
+                if (last) {
+                    const half8 hv = *(const half8*)(l.hi + t * PITCH + 16 * c);
+                    const half8 lv = *(const half8*)(l.lo + t * PITCH + 16 * c);
+                    int64_t xr, ro;
+                    token(t, xr, ro);
+                    floatx4 lo4, hi4;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float rv = (float)hv[e] + (st > 0 ? (float)lv[e] : 0.0f) - (float)cv[e];
+                        if (e < 4) lo4[e] = rv; else hi4[e - 4] = rv;
+                    }
+                    *(floatx4*)(residual + ro * D + 8 * c) = lo4;
+                    *(floatx4*)(residual + ro * D + 8 * c + 4) = hi4;
+                } else if (st == 0) {
+                    *(half8*)(l.lo + t * PITCH + 16 * c) = -cv;
+                } else {
+                    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+                    const u32x4 a = *(const u32x4*)(l.hi + t * PITCH + 16 * c), bb = *(const u32x4*)(l.lo + t * PITCH + 16 * c),
+                                cc = __builtin_bit_cast(u32x4, cv);
+                    u32x4 na, nb;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        uint32_t p, q;
+                        resplit2(a[w], bb[w], cc[w], p, q);
+                        na[w] = p;
+                        nb[w] = q;
+                    }
+                    *(u32x4*)(l.hi + t * PITCH + 16 * c) = na;
+                    *(u32x4*)(l.lo + t * PITCH + 16 * c) = nb;
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
 // Fused encode parameters (points == nullptr: assignment only).
 struct EncArgs {
     double2* points;
@@ -977,6 +1216,39 @@ int launch_rvq_small(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const u
     return launch_status();
 }
 
+// Whether a call of at most 32 tokens per work item takes rvq_few_kernel.  It
+// does once there are more items than the staged form has resident blocks (one
+// or two per compute unit): that form then runs them in rounds.  Below that,
+// the staged form starts all its copies at once and only loses at d <= 64,
+// where its two-tile waves scan 64 columns for a few tokens.  Measured, staged
+// and few (us): d = 128, S = 3, K = 256, 512 items of 4 tokens 36.0 and 21.4,
+// 300 of 16 31.7 and 22.3, 144 of 16 13.6 and 14.9; 2048 streams of 32 tokens
+// 160 and 79.  d = 64, S = 2, K = 256, 288 items of 1 token 7.0 and 6.1, 144 of
+// 16 9.9 and 8.5, 300 of 32 11.7 and 13.1.  Small books keep their own kernel
+// in the per-stream form (K = 64, 2304 streams of 32 tokens: 14.0 and 15.8).
+template <int D>
+bool few_tokens(const fkv_rvq_desc* dsc, int ns, const GroupArgs& grp)
+{
+    const int64_t Ta = dsc->t_end - dsc->t_begin, n_items = grp.on ? grp.n_groups : dsc->n_streams;
+    if (Ta > kFewTokens || (grp.on && grp.G * Ta > kFewTokens)) return false;
+    if (!grp.on && D <= 64 && dsc->K <= kSmallK && ns <= 2) return false;
+    return n_items > 256 * Cfg<D>::MIN_BLOCKS || (D <= 64 && (grp.on ? grp.G : 1) * Ta <= 16);
+}
+
+template <int D, bool GRP>
+int launch_rvq_few(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint16_t* books,
+                   const int32_t* stream_book, uint8_t* symbols, float* residual, uint32_t* n_bad,
+                   const GroupArgs& grp, hipStream_t stream)
+{
+    const int waves = (dsc->K + 31) / 32;
+    const int64_t n_items = GRP ? grp.n_groups : dsc->n_streams;
+    hipLaunchKernelGGL((rvq_few_kernel<D, GRP>), dim3((unsigned)std::min<int64_t>(n_items, 1 << 20)), dim3(64 * waves),
+                       0, stream, (const _Float16*)x, (const _Float16*)books, stream_book, symbols, residual, n_bad,
+                       dsc->T, dsc->t_begin, dsc->t_end - dsc->t_begin, dsc->S, ns, dsc->K, dsc->n_books, grp.groups,
+                       grp.G, dsc->n_streams, n_items);
+    return launch_status();
+}
+
 template <int D>
 int launch_rvq(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint16_t* books,
                const int32_t* stream_book, uint8_t* symbols, float* residual, uint32_t* n_bad,
@@ -984,6 +1256,11 @@ int launch_rvq(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint16_
 {
     // ns stages are assigned (the first ns of the S in the layout); the hi/lo
     // residual is needed only from a third stage on
+    if (!enc.points && few_tokens<D>(dsc, ns, grp)) {
+        if (grp.on)
+            return launch_rvq_few<D, true>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, grp, stream);
+        return launch_rvq_few<D, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, grp, stream);
+    }
     if (grp.on) {
         if (ns <= 2)
             return launch_rvq_t<D, false, false, true>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,

@@ -59,6 +59,50 @@ def test_groups_equal_per_stream(fkv, d, S, K, T, t0, t1, G):
     assert np.array_equal(got[listed], want[listed]) and (got[~listed] == 0xA5).all()
 
 
+@pytest.mark.parametrize("d,S,K,n", [
+    (16, 1, 1, 1), (32, 3, 33, 2), (48, 2, 64, 31), (64, 2, 256, 1), (64, 4, 256, 32), (80, 3, 97, 5), (96, 2, 100, 4),
+    (112, 5, 129, 3), (128, 3, 256, 4), (128, 2, 200, 32), (128, 8, 256, 7), (144, 3, 255, 2), (192, 4, 64, 6),
+    (208, 2, 160, 1), (256, 3, 256, 4), (256, 8, 31, 32),
+])
+def test_few_tokens_equal_bulk(fkv, d, S, K, n):
+    """At most 32 tokens per work item (per stream, or per group of streams) against the bulk form over a
+    longer range that holds them: the arithmetic of a token does not depend on the other tokens, so symbols
+    and residuals are equal bit for bit.  Tied codewords, zero vectors, a stream and a group without a book,
+    and fewer stages than the layout holds."""
+    rng = np.random.default_rng(d + 5 * S + K + n)
+    nb, ns, T, t0 = 3, 520, 75, 11                      # more streams than resident blocks of the staged form
+    x = (rng.standard_normal((ns, T, d)) * 2).astype(np.float16)
+    x[1, t0] = 0
+    books = (rng.standard_normal((nb, S, K, d)) * (0.5 ** np.arange(S))[None, :, None, None]).astype(np.float16)
+    books[1, :, K // 2] = books[1, :, 0]                # equal codewords: the lower index wins
+    sb = np.tile(np.array([0, 1, 2, 1, 0, 2, 1, 2], np.int32), ns // 8)
+    sb[5] = 9                                           # no book
+    xd, bd, sd = dev(x), dev(books), dev(sb)
+    full, fres = fkv.fkv_rvq_assign(xd, bd, sd, 0, T, want_residual=True)
+    full, fres = host(full).reshape(ns, T, S)[:, t0:t0 + n], host(fres)[:, t0:t0 + n]
+    nbad = torch.zeros(1, dtype=torch.int32, device="cuda")
+    sym, res = fkv.fkv_rvq_assign(xd, bd, sd, t0, t0 + n, want_residual=True, n_bad=nbad)
+    assert np.array_equal(host(sym).reshape(ns, n, S), full) and int(host(nbad)[0]) == 1
+    assert np.array_equal(host(res).view(np.uint32), fres.view(np.uint32))
+    k = max(1, S - 1)
+    sym = torch.full((ns, n * S), 0xA5, dtype=torch.uint8, device="cuda")
+    fkv.fkv_rvq_assign(xd, bd, sd, t0, t0 + n, symbols=sym, n_stages=k)
+    got = host(sym).reshape(ns, n, S)
+    valid = np.arange(ns) != 5
+    assert np.array_equal(got[..., :k], full[..., :k]) and (got[valid][..., k:] == 0xA5).all()
+    if 2 * n <= 32:
+        some = np.array([[0, 4], [3, 6], [2, 7], [5, 1]], np.int32)   # the last one mixes books
+        groups = dev(np.tile(some, (130, 1)))           # (the same bytes written again)
+        nbad.zero_()
+        sym = torch.full((ns, n * S), 0xA5, dtype=torch.uint8, device="cuda")
+        res = torch.zeros((ns, n, d), dtype=torch.float32, device="cuda")
+        fkv.fkv_rvq_assign_groups(xd, bd, sd, groups, t0, t0 + n, symbols=sym, residual=res, n_bad=nbad)
+        got, gr, listed = host(sym).reshape(ns, n, S), host(res), [0, 4, 3, 6, 2, 7]
+        assert np.array_equal(got[listed], full[listed]) and int(host(nbad)[0]) == 130
+        assert np.array_equal(gr[listed].view(np.uint32), fres[listed].view(np.uint32))
+        assert (got[[1, 5]] == 0xFF).all() and np.isnan(gr[[1, 5]]).all()
+
+
 def test_groups_invalid(fkv):
     rng = np.random.default_rng(3)
     d, S, K, T, nb, ns = 64, 2, 64, 20, 2, 6
