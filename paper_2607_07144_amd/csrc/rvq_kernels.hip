@@ -62,6 +62,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kLdsBudget = 160 * 1024;
 constexpr float kBiasHiScale = 16384.0f;   // weight of the bias's second fp16 slot
+constexpr int kItemTokens = 256;           // tokens per block of the staged kernels
 constexpr int kMaxGroup = 256;             // streams per group in the grouped form (<= threads per block)
 
 // One LDS book buffer: Kp rows of row_p bytes, then a 16-byte zero pad.
@@ -71,7 +72,7 @@ __host__ __device__ constexpr size_t buf_bytes_of(int row_p, int Kp)
 }
 
 template <int D>
-struct Cfg {
+struct Shape {
     static constexpr int KS = D / 16;                    // 16-deep matrix steps along d
     static constexpr int NCH = D / 8;                    // 16-byte chunks of a codeword
     // LDS row: the codeword's NCH chunks, then its bias-step A chunk.  The odd
@@ -80,19 +81,37 @@ struct Cfg {
     // swizzle and a lane's fragments sit at fixed offsets from one base.
     static constexpr int ROW_P = (NCH + 1) * 16;
     static constexpr int TILE_P = 32 * ROW_P;            // one 32-codeword tile
-    static constexpr int TT = D <= 64 ? 2 : 1;           // 32-token tiles per wave
-    static constexpr int WAVES = D <= 64 ? 4 : 8;
-    static constexpr int THREADS = 64 * WAVES;
-    static constexpr int TOK = WAVES * TT * 32;          // tokens per block
-    static constexpr int MIN_BLOCKS = 8 / WAVES;         // two waves per SIMD
-    // two book buffers when two full (K = 256) books fit, else one
-    static constexpr int NBUF = 2 * buf_bytes_of(ROW_P, 256) <= kLdsBudget ? 2 : 1;
 };
 
-template <int D>
+// Block shapes.  The narrow one (four waves of two token tiles, two blocks per
+// compute unit, three at d <= 64) serves large launches: a fragment read from
+// LDS feeds two token tiles, and while one block waits for its rows or the next
+// book the other has the matrix cores.  The wide one (eight waves of one token
+// tile, one block per compute unit, two book buffers) serves d > 128, where two
+// token tiles do not fit the registers, and launches of at most one block per
+// compute unit, where twice the waves share a block's 256 tokens.
+// Measured, wide and narrow, 256-token items (us): d = 128, S = 3, K = 256:
+// 2^18 items 22.0-22.9 and 20.0-20.4 ms (602 -> 650 TFLOP/s); 2048 items 182
+// and 160, 384 items 44.9 and 40.8, 256 items 26.4 and 27.5, 64 items 19.6 and
+// 22.4.  d = 80, S = 3, K = 100: 512 items 21.9 and 19.0, 256 items 9.9 and 11.7.
+// One 8-wave block of two token tiles per compute unit (512 tokens a book pass)
+// instead of two 4-wave blocks: 22.2 ms, its waves wait at the same barriers.
+template <int D, bool WIDE>
+struct Cfg : Shape<D> {
+    using Shape<D>::ROW_P;
+    static constexpr int TT = WIDE ? 1 : 2;              // 32-token tiles per wave
+    static constexpr int WAVES = WIDE ? 8 : 4;
+    static constexpr int THREADS = 64 * WAVES;
+    static_assert(WAVES * TT * 32 == kItemTokens, "a block takes one item");
+    static constexpr int BLOCKS = WIDE ? 1 : D <= 64 ? 3 : 2;   // resident blocks per compute unit
+    // two book buffers when two full (K = 256) books fit, else one
+    static constexpr int NBUF = BLOCKS * 2 * buf_bytes_of(ROW_P, 256) <= kLdsBudget ? 2 : 1;
+};
+
+template <int D, bool WIDE>
 size_t lds_bytes(int Kp)
 {
-    return (size_t)Cfg<D>::NBUF * buf_bytes_of(Cfg<D>::ROW_P, Kp);
+    return (size_t)Cfg<D, WIDE>::NBUF * buf_bytes_of(Cfg<D, WIDE>::ROW_P, Kp);
 }
 
 // Asynchronously copies stage codebook C ([K][D] fp16) into an LDS buffer of
@@ -100,11 +119,11 @@ size_t lds_bytes(int Kp)
 // row's bias-step slot gets a placeholder (its last data chunk) that
 // book_bias_rows overwrites, and rows >= K are copies of row K-1, so they tie
 // with it and lose to its lower index.
-template <int D>
+template <int D, int WAVES>
 __device__ __forceinline__ void book_to_lds_async(const _Float16* __restrict__ C, int K, int Kp,
                                                   uint8_t* buf, int wave, int lane)
 {
-    constexpr int NCH = Cfg<D>::NCH, CH = NCH + 1, STEP = Cfg<D>::WAVES * 64;
+    constexpr int NCH = Shape<D>::NCH, CH = NCH + 1, STEP = WAVES * 64;
     const int chunks = Kp * CH;   // a multiple of 64 (Kp is)
     for (int q0 = __builtin_amdgcn_readfirstlane(wave) * 64; q0 < chunks; q0 += STEP) {
         const uint32_t q = (uint32_t)(q0 + lane);
@@ -137,12 +156,12 @@ __device__ __forceinline__ half8 bias_row(float acc)
 
 // The bias-step A chunk of every row of NB buffers, written into the row's last slot.  All rows'
 // LDS reads are issued before any norm is formed, so their latencies overlap.
-template <int D, int NB>
+template <int D, int THREADS, int NB>
 __device__ __forceinline__ void book_bias_rows(uint8_t* buf0, uint8_t* buf1, int Kp)
 {
-    constexpr int NCH = Cfg<D>::NCH;
-    for (int r = threadIdx.x; r < Kp; r += Cfg<D>::THREADS) {
-        uint8_t* row[2] = {buf0 + (size_t)r * Cfg<D>::ROW_P, buf1 + (size_t)r * Cfg<D>::ROW_P};
+    constexpr int NCH = Shape<D>::NCH;
+    for (int r = threadIdx.x; r < Kp; r += THREADS) {
+        uint8_t* row[2] = {buf0 + (size_t)r * Shape<D>::ROW_P, buf1 + (size_t)r * Shape<D>::ROW_P};
         half8 v[NB][NCH];
 #pragma unroll
         for (int b = 0; b < NB; ++b)
@@ -198,7 +217,7 @@ __device__ __forceinline__ void wait_all_and_sync()
 // bias step.
 template <int D>
 struct Frag {
-    half8 a[Cfg<D>::KS];
+    half8 a[Shape<D>::KS];
     half8 bias;
 };
 
@@ -210,24 +229,24 @@ struct Frag {
 template <int D>
 __device__ __forceinline__ void load_frag(Frag<D>& f, const uint8_t* buf, uint32_t base, int ct)
 {
-    const uint8_t* tile = buf + base + (size_t)ct * Cfg<D>::TILE_P;
+    const uint8_t* tile = buf + base + (size_t)ct * Shape<D>::TILE_P;
 #pragma unroll
-    for (int ks = 0; ks < Cfg<D>::KS; ++ks) f.a[ks] = *(const half8*)(tile + ks * 32);
-    f.bias = *(const half8*)(tile + Cfg<D>::NCH * 16);
+    for (int ks = 0; ks < Shape<D>::KS; ++ks) f.a[ks] = *(const half8*)(tile + ks * 32);
+    f.bias = *(const half8*)(tile + Shape<D>::NCH * 16);
 }
 
 // acc[tt] = bias step + A(tile) x B(tt) over all k-steps; with TWO a second B
 // operand accumulates into the same tile.
 template <int D, int TT, bool TWO>
 __device__ __forceinline__ void issue_tile(const Frag<D>& f, const half8 (&bz)[TT],
-                                           const half8 (&bA)[TT][Cfg<D>::KS],
-                                           const half8 (&bB)[TT][Cfg<D>::KS], floatx16 (&acc)[TT])
+                                           const half8 (&bA)[TT][Shape<D>::KS],
+                                           const half8 (&bB)[TT][Shape<D>::KS], floatx16 (&acc)[TT])
 {
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt)
         acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.bias, bz[tt], (floatx16)0.0f, 0, 0, 0);
 #pragma unroll
-    for (int ks = 0; ks < Cfg<D>::KS; ++ks) {
+    for (int ks = 0; ks < Shape<D>::KS; ++ks) {
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt)
             acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.a[ks], bA[tt][ks], acc[tt], 0, 0, 0);
@@ -285,14 +304,14 @@ __device__ __forceinline__ void pair_second(const floatx16 (&acc)[TT], const uin
 // being issued is followed by a few VALU ops of the previous tile's argmin and,
 // early on, the LDS reads of the next tile's fragments, so one wave keeps its
 // matrix core busy while its vector ALU and LDS work proceed.
-template <int NMFMA, int NVALU, int NDS>
+template <int NMFMA, int NVALU, int NDS, int GAP>
 __device__ __forceinline__ void interleave_hint()
 {
     constexpr int per = (NVALU + NMFMA - 1) / NMFMA;
 #pragma unroll
     for (int i = 0; i < NMFMA; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one MFMA
-        if (i < NDS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
+        if (i % GAP == 0 && i / GAP < NDS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
         __builtin_amdgcn_sched_group_barrier(0x002, per, 0);    // a few VALU
     }
 }
@@ -302,13 +321,13 @@ __device__ __forceinline__ void interleave_hint()
 // argmin of tile ct executes on the VALU.  Tiles 2p and 2p+1 form pair p.
 template <int D, int TT, bool TWO>
 __device__ __forceinline__ void stage_scan(const uint8_t* buf, uint32_t fa, int nct,
-                                           const half8 (&bz)[TT], const half8 (&bA)[TT][Cfg<D>::KS],
-                                           const half8 (&bB)[TT][Cfg<D>::KS], uint32_t (&bkey)[TT],
+                                           const half8 (&bz)[TT], const half8 (&bA)[TT][Shape<D>::KS],
+                                           const half8 (&bB)[TT][Shape<D>::KS], uint32_t (&bkey)[TT],
                                            int (&bpair)[TT])
 {
-    constexpr int NM = TT * (1 + Cfg<D>::KS * (TWO ? 2 : 1));   // MFMAs per tile
+    constexpr int NM = TT * (1 + Shape<D>::KS * (TWO ? 2 : 1));   // MFMAs per tile
     constexpr int NV = TT * 26;                                 // VALU ops of one tile's argmin
-    constexpr int ND = Cfg<D>::KS + 1;                          // LDS reads of one tile's fragments
+    constexpr int ND = Shape<D>::KS + 1;                          // LDS reads of one tile's fragments
     Frag<D> f0, f1;
     floatx16 acc0[TT], acc1[TT];
     uint32_t pk[TT];
@@ -320,15 +339,86 @@ __device__ __forceinline__ void stage_scan(const uint8_t* buf, uint32_t fa, int 
         issue_tile<D, TT, TWO>(f1, bz, bA, bB, acc1);
         load_frag<D>(f0, buf, fa, ct + 2);
         pair_first<TT>(acc0, pk);
-        interleave_hint<NM, NV, ND>();
+        interleave_hint<NM, NV, ND, 1>();
         issue_tile<D, TT, TWO>(f0, bz, bA, bB, acc0);
         load_frag<D>(f1, buf, fa, min(ct + 3, nct - 1));
         pair_second<TT>(acc1, pk, ct >> 1, bkey, bpair);
-        interleave_hint<NM, NV, ND>();
+        interleave_hint<NM, NV, ND, 1>();
     }
     issue_tile<D, TT, TWO>(f1, bz, bA, bB, acc1);
     pair_first<TT>(acc0, pk);
     pair_second<TT>(acc1, pk, ct >> 1, bkey, bpair);
+}
+
+// The same for one token tile.
+template <int D, bool TWO>
+__device__ __forceinline__ void issue_one(const Frag<D>& f, const half8& bz, const half8 (&bA)[Shape<D>::KS],
+                                          const half8 (&bB)[Shape<D>::KS], floatx16& acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.bias, bz, (floatx16)0.0f, 0, 0, 0);
+#pragma unroll
+    for (int ks = 0; ks < Shape<D>::KS; ++ks) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.a[ks], bA[ks], acc, 0, 0, 0);
+        if (TWO) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.a[ks], bB[ks], acc, 0, 0, 0);
+    }
+}
+
+// One stage's scores for two token tiles with one fragment buffer and one
+// accumulator per token tile: while token tile 1 takes codeword tile ct, token
+// tile 0's scores of it are reduced and each fragment, used for the last time,
+// is replaced by the next codeword tile's; then token tile 0 takes that one
+// while token tile 1 is reduced.  Half the LDS reads of two one-tile scans, and
+// 196 registers at d = 128 beside the keys, so that two waves fit a SIMD.
+template <int D, bool TWO>
+__device__ __forceinline__ void stage_scan_two(const uint8_t* buf, uint32_t fa, int nct, const half8 (&bz)[2],
+                                               const half8 (&bA)[2][Shape<D>::KS], const half8 (&bB)[2][Shape<D>::KS],
+                                               uint32_t (&bkey)[2], int (&bpair)[2])
+{
+    constexpr int NM = 1 + Shape<D>::KS * (TWO ? 2 : 1);   // MFMAs per codeword tile and token tile
+    constexpr int ND = Shape<D>::KS + 1;                   // LDS reads of one tile's fragments
+    constexpr int GAP = TWO ? 2 : 1;                       // MFMAs per fragment
+    Frag<D> f;
+    floatx16 a0, a1;
+    uint32_t pk[2];
+    auto issue0 = [&] { issue_one<D, TWO>(f, bz[0], bA[0], bB[0], a0); };
+    auto issue1 = [&] { issue_one<D, TWO>(f, bz[1], bA[1], bB[1], a1); };
+    auto first = [&](int tt, const floatx16& a) { pk[tt] = tile_min_key<0>(a); };
+    auto second = [&](int tt, const floatx16& a, int pair) {
+        const uint32_t k = min(pk[tt], tile_min_key<16>(a));
+        if ((k & ~31u) < (bkey[tt] & ~31u)) {
+            bkey[tt] = k;
+            bpair[tt] = pair;
+        }
+    };
+    load_frag<D>(f, buf, fa, 0);
+    issue0();
+    int ct = 0;
+    for (; ct + 2 < nct; ct += 2) {
+        issue1();
+        load_frag<D>(f, buf, fa, ct + 1);
+        first(0, a0);
+        interleave_hint<NM, 26, ND, GAP>();
+        issue0();
+        first(1, a1);
+        interleave_hint<NM, 26, 0, 1>();
+        issue1();
+        load_frag<D>(f, buf, fa, ct + 2);
+        second(0, a0, ct >> 1);
+        interleave_hint<NM, 30, ND, GAP>();
+        issue0();
+        second(1, a1, ct >> 1);
+        interleave_hint<NM, 30, 0, 1>();
+    }
+    issue1();
+    load_frag<D>(f, buf, fa, ct + 1);
+    first(0, a0);
+    interleave_hint<NM, 26, ND, GAP>();
+    issue0();
+    first(1, a1);
+    interleave_hint<NM, 26, 0, 1>();
+    issue1();
+    second(0, a0, ct >> 1);
+    second(1, a1, ct >> 1);
 }
 
 // Re-split of a residual pair: for the two fp16 lanes q of the words a (hi),
@@ -356,8 +446,11 @@ __device__ __forceinline__ void resplit2(uint32_t a, uint32_t b, uint32_t c, uin
 // + e] is member e of group g) and its tokens are the members' archived
 // tokens, member by member, so that one block serves all of them with a single
 // copy of the book (the per-token arithmetic is that of the per-stream form).
-template <int D, bool HILO, bool ENC, bool GRP>
-__global__ __launch_bounds__(Cfg<D>::THREADS, Cfg<D>::MIN_BLOCKS) void rvq_assign_kernel(
+template <int D, bool WIDE, bool ENC, bool GRP>
+constexpr bool kPers = WIDE && D > 128 && !ENC && !GRP;
+
+template <int D, bool WIDE, bool ENC, bool GRP>
+__global__ __launch_bounds__((Cfg<D, WIDE>::THREADS), (Cfg<D, WIDE>::BLOCKS)) void rvq_assign_kernel(
     const _Float16* __restrict__ x, const _Float16* __restrict__ books,
     const int32_t* __restrict__ stream_book, uint8_t* __restrict__ symbols,
     float* __restrict__ residual, uint32_t* __restrict__ n_bad, int64_t T, int64_t t_begin,
@@ -366,14 +459,13 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, Cfg<D>::MIN_BLOCKS) void rvq_assig
     const int32_t* __restrict__ groups, int G, int64_t n_streams, int64_t ipb, int64_t n_items)
 {
     static_assert(!(GRP && ENC), "the grouped form has no fused encode");
-    using C = Cfg<D>;
+    using C = Cfg<D, WIDE>;
     // PERS: a block takes ipb consecutive work items (token ranges, mostly of
     // one stream) and loads the next item's token rows into registers during
     // the current item's last stage, so a new item does not start by waiting
-    // on HBM.  Only the hi/lo per-stream instances hold the extra registers
-    // without spilling.
-    constexpr bool PERS = HILO && !ENC && !GRP;
-    constexpr int KS = C::KS, TT = C::TT, TOK = C::TOK, NBUF = C::NBUF;
+    // on HBM.  (In the narrow shape the other block's scans cover that wait.)
+    constexpr bool PERS = kPers<D, WIDE, ENC, GRP>;
+    constexpr int KS = C::KS, TT = C::TT, NBUF = C::NBUF;
     extern __shared__ __align__(16) uint8_t lds[];
     // LDS: NBUF buffers of Kp rows (codeword + bias-step chunk) and a zero
     // pad; addressed from `lds` so every access stays an LDS access.
@@ -480,8 +572,8 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, Cfg<D>::MIN_BLOCKS) void rvq_assig
         if (ENC && tid < 256) V_l[tid] = tid < cN ? vtab[tid] : make_double2(NAN, NAN);
 
         // start the first books' copies; zero the buffers' end pads
-        book_to_lds_async<D>(bk, K, Kp, lds, wave, lane);
-        if (NBUF > 1 && NS > 1) book_to_lds_async<D>(bk + (size_t)K * D, K, Kp, lds + buf_bytes, wave, lane);
+        book_to_lds_async<D, C::WAVES>(bk, K, Kp, lds, wave, lane);
+        if (NBUF > 1 && NS > 1) book_to_lds_async<D, C::WAVES>(bk + (size_t)K * D, K, Kp, lds + buf_bytes, wave, lane);
         if (tid < NBUF) *(half8*)(lds + tid * buf_bytes + (size_t)Kp * C::ROW_P) = (half8)(_Float16)0;
 
 #pragma unroll
@@ -502,9 +594,9 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, Cfg<D>::MIN_BLOCKS) void rvq_assig
 
         wait_all_and_sync();
         if (NBUF > 1 && NS > 1)
-            book_bias_rows<D, 2>(lds, lds + buf_bytes, Kp);
+            book_bias_rows<D, C::THREADS, 2>(lds, lds + buf_bytes, Kp);
         else
-            book_bias_rows<D, 1>(lds, lds, Kp);
+            book_bias_rows<D, C::THREADS, 1>(lds, lds, Kp);
         __syncthreads();
 
         const int nct = Kp / 32;  // even
@@ -544,7 +636,10 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, Cfg<D>::MIN_BLOCKS) void rvq_assig
                 bpair[tt] = 0;
             }
             if (wave_on) {
-                stage_scan<D, TT, TWO>(buf, fa, nct, bz, bA, bB, bkey, bpair);
+                if constexpr (TT == 2)
+                    stage_scan_two<D, TWO>(buf, fa, nct, bz, bA, bB, bkey, bpair);
+                else
+                    stage_scan<D, TT, TWO>(buf, fa, nct, bz, bA, bB, bkey, bpair);
 #pragma unroll
                 for (int tt = 0; tt < TT; ++tt) {
                     const int li = (int)(bkey[tt] & 31u);
@@ -572,7 +667,7 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, Cfg<D>::MIN_BLOCKS) void rvq_assig
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks) cv[ks] = *(const half8*)(crow + ks * 32);
                     const bool last = st + 1 == NS;
-                    if (HILO && TWO && !last) {
+                    if (TWO && !last) {
                         // r = (hi + lo) - c for st >= 2, (x - c_0) - c_1 for st == 1; split again
 #pragma unroll
                         for (int ks = 0; ks < KS; ++ks) {
@@ -616,14 +711,14 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, Cfg<D>::MIN_BLOCKS) void rvq_assig
                 // Book pipeline: buffer `cur` is free once every wave is past here.
                 wait_all_and_sync();
                 if (NBUF == 1) {
-                    book_to_lds_async<D>(bk + (size_t)(st + 1) * K * D, K, Kp, lds, wave, lane);
+                    book_to_lds_async<D, C::WAVES>(bk + (size_t)(st + 1) * K * D, K, Kp, lds, wave, lane);
                     wait_all_and_sync();
                 } else if (st + 2 < NS) {
-                    book_to_lds_async<D>(bk + (size_t)(st + 2) * K * D, K, Kp, lds + cur * buf_bytes, wave, lane);
+                    book_to_lds_async<D, C::WAVES>(bk + (size_t)(st + 2) * K * D, K, Kp, lds + cur * buf_bytes, wave, lane);
                 }
                 if (NBUF == 1 || st >= 1) {
                     uint8_t* nb = lds + (NBUF > 1 ? ((st + 1) & 1) : 0) * buf_bytes;
-                    book_bias_rows<D, 1>(nb, nb, Kp);
+                    book_bias_rows<D, C::THREADS, 1>(nb, nb, Kp);
                 }
                 __syncthreads();
             }
@@ -668,10 +763,9 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, Cfg<D>::MIN_BLOCKS) void rvq_assig
 
 // LDS after the book buffers for the fused span encode: 256 vertices and the
 // block's symbols.
-template <int D>
 constexpr size_t enc_lds_bytes()
 {
-    return 256 * 16 + (size_t)Cfg<D>::TOK * 8;
+    return 256 * 16 + (size_t)kItemTokens * 8;
 }
 
 // ---- small books: at most 64 codewords and two stages (d <= 64) ----------
@@ -688,7 +782,7 @@ constexpr int kSmallMaxItems = 8;   // token items per block (bounds the symbol 
 // fragment buffer.
 template <int D, bool TWO>
 __device__ __forceinline__ void stage_scan_small(const uint8_t* buf, uint32_t fa, const half8 (&bz)[1],
-                                                 const half8 (&bA)[1][Cfg<D>::KS], const half8 (&bB)[1][Cfg<D>::KS],
+                                                 const half8 (&bA)[1][Shape<D>::KS], const half8 (&bB)[1][Shape<D>::KS],
                                                  uint32_t (&bkey)[1], int (&bpair)[1])
 {
     Frag<D> f;
@@ -711,23 +805,23 @@ __device__ __forceinline__ void lds_barrier()
 }
 
 template <int D>
-__device__ __forceinline__ void load_rows(half8 (&dst)[Cfg<D>::KS], const _Float16* __restrict__ x, int64_t row,
+__device__ __forceinline__ void load_rows(half8 (&dst)[Shape<D>::KS], const _Float16* __restrict__ x, int64_t row,
                                           bool valid, int hh)
 {
     const _Float16* p = x + row * D + 8 * hh;
 #pragma unroll
-    for (int ks = 0; ks < Cfg<D>::KS; ++ks) dst[ks] = valid ? *(const half8*)(p + 16 * ks) : (half8)(_Float16)0;
+    for (int ks = 0; ks < Shape<D>::KS; ++ks) dst[ks] = valid ? *(const half8*)(p + 16 * ks) : (half8)(_Float16)0;
 }
 
 template <int D, bool ENC>
-__global__ __launch_bounds__(Cfg<D>::THREADS, kSmallBlocks) void rvq_small_kernel(
+__global__ __launch_bounds__((Cfg<D, false>::THREADS), kSmallBlocks) void rvq_small_kernel(
     const _Float16* __restrict__ x, const _Float16* __restrict__ books, const int32_t* __restrict__ stream_book,
     uint8_t* __restrict__ symbols, float* __restrict__ residual, uint32_t* __restrict__ n_bad, int64_t T,
     int64_t t_begin, int64_t Ta, int S, int NS, int K, int Kp, int n_books, int64_t blocks_per_stream, int64_t tpi,
     int64_t ipb, double2* __restrict__ points, const double2* __restrict__ vtab, double cr, int cN, int cL,
     int64_t n_spans)
 {
-    using C = Cfg<D>;
+    using C = Cfg<D, false>;
     constexpr int KS = C::KS, TOK = C::WAVES * 32;
     extern __shared__ __align__(16) uint8_t lds[];
     const size_t buf_bytes = buf_bytes_of(C::ROW_P, Kp);
@@ -764,14 +858,14 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, kSmallBlocks) void rvq_small_kerne
     double2* V_l = (double2*)(lds + 2 * buf_bytes);
     uint8_t* sym_l = (uint8_t*)(V_l + 256);   // the block's symbols, token-major from tb0
     if (ENC && tid < 256) V_l[tid] = tid < cN ? vtab[tid] : make_double2(NAN, NAN);
-    book_to_lds_async<D>(bk, K, Kp, lds, wave, lane);
-    if (NS > 1) book_to_lds_async<D>(bk + (size_t)K * D, K, Kp, lds + buf_bytes, wave, lane);
+    book_to_lds_async<D, C::WAVES>(bk, K, Kp, lds, wave, lane);
+    if (NS > 1) book_to_lds_async<D, C::WAVES>(bk + (size_t)K * D, K, Kp, lds + buf_bytes, wave, lane);
     if (tid < 2) *(half8*)(lds + tid * buf_bytes + (size_t)Kp * C::ROW_P) = (half8)(_Float16)0;
     wait_all_and_sync();
     if (NS > 1)
-        book_bias_rows<D, 2>(lds, lds + buf_bytes, Kp);
+        book_bias_rows<D, C::THREADS, 2>(lds, lds + buf_bytes, Kp);
     else
-        book_bias_rows<D, 1>(lds, lds, Kp);
+        book_bias_rows<D, C::THREADS, 1>(lds, lds, Kp);
     __syncthreads();
 
     const uint32_t fa = (uint32_t)(col * C::ROW_P + hh * 16);
@@ -1133,7 +1227,7 @@ struct GroupArgs {
     int G;
 };
 
-template <int D, bool HILO, bool ENC, bool GRP>
+template <int D, bool WIDE, bool ENC, bool GRP>
 int launch_rvq_t(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint16_t* books,
                  const int32_t* stream_book, uint8_t* symbols, float* residual, uint32_t* n_bad,
                  const EncArgs& enc, const GroupArgs& grp, hipStream_t stream)
@@ -1141,15 +1235,15 @@ int launch_rvq_t(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint1
     static std::once_flag once;
     const int Kp = (dsc->K + 63) / 64 * 64;  // whole pairs of 32-codeword tiles
     std::call_once(once, [] {
-        (void)hipFuncSetAttribute((const void*)rvq_assign_kernel<D, HILO, ENC, GRP>,
+        (void)hipFuncSetAttribute((const void*)rvq_assign_kernel<D, WIDE, ENC, GRP>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)(lds_bytes<D>(256) + (ENC ? enc_lds_bytes<D>() : 0)));
+                                  (int)(lds_bytes<D, WIDE>(256) + (ENC ? enc_lds_bytes() : 0)));
     });
     (void)hipGetLastError();
     const int64_t Ta = dsc->t_end - dsc->t_begin;
     // Tokens per block: with the fused encode, a multiple of L / gcd(L, S) so
     // that every block holds whole spans.
-    int64_t tpb = Cfg<D>::TOK;
+    int64_t tpb = kItemTokens;
     if (ENC) {
         int a = enc.L, b = dsc->S;
         while (b) {
@@ -1158,19 +1252,19 @@ int launch_rvq_t(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint1
             b = t;
         }
         const int unit = enc.L / a;
-        tpb = (int64_t)(Cfg<D>::TOK / unit) * unit;
+        tpb = (int64_t)(kItemTokens / unit) * unit;
     }
     const int64_t items = GRP ? grp.n_groups : dsc->n_streams;
     const int64_t bps = ((GRP ? grp.G * Ta : Ta) + tpb - 1) / tpb;
     const int64_t n_items = bps * items;
     // 16 items per block once there are at least 64 blocks' worth per compute
-    // unit (2-3.5% faster at the long-context shape than one item per block)
-    const int64_t ipb = (HILO && !ENC && !GRP && n_items >= 256 * 64) ? 16 : 1;
+    // unit
+    const int64_t ipb = (kPers<D, WIDE, ENC, GRP> && ns > 2 && n_items >= 256 * 64) ? 16 : 1;
     const int64_t nblk = (n_items + ipb - 1) / ipb;
     if (nblk > 0x7fffffff) return FKV_ERR_UNSUPPORTED;
     const int64_t n_spans = ENC ? (Ta * dsc->S + enc.L - 1) / enc.L : 0;
-    const size_t shm = lds_bytes<D>(Kp) + (ENC ? enc_lds_bytes<D>() : 0);
-    hipLaunchKernelGGL((rvq_assign_kernel<D, HILO, ENC, GRP>), dim3((unsigned)nblk), dim3(Cfg<D>::THREADS), shm,
+    const size_t shm = lds_bytes<D, WIDE>(Kp) + (ENC ? enc_lds_bytes() : 0);
+    hipLaunchKernelGGL((rvq_assign_kernel<D, WIDE, ENC, GRP>), dim3((unsigned)nblk), dim3(Cfg<D, WIDE>::THREADS), shm,
                        stream, (const _Float16*)x, (const _Float16*)books, stream_book, symbols, residual, n_bad,
                        dsc->T, dsc->t_begin, Ta, dsc->S, ns, dsc->K, Kp, dsc->n_books, bps, tpb, enc.points, enc.vtab,
                        enc.r, enc.N, enc.L, n_spans, grp.groups, grp.G, dsc->n_streams, ipb, n_items);
@@ -1185,7 +1279,7 @@ int launch_rvq_small(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const u
                      const int32_t* stream_book, uint8_t* symbols, float* residual, uint32_t* n_bad,
                      const EncArgs& enc, hipStream_t stream)
 {
-    constexpr int TOK = Cfg<D>::WAVES * 32;
+    constexpr int TOK = Cfg<D, false>::WAVES * 32;
     const int Kp = 64;
     const int64_t Ta = dsc->t_end - dsc->t_begin;
     int64_t tpi = TOK;
@@ -1208,8 +1302,8 @@ int launch_rvq_small(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const u
     const int64_t nblk = bps * dsc->n_streams;
     if (nblk > 0x7fffffff) return FKV_ERR_UNSUPPORTED;
     const int64_t n_spans = ENC ? (Ta * dsc->S + enc.L - 1) / enc.L : 0;
-    const size_t shm = 2 * buf_bytes_of(Cfg<D>::ROW_P, Kp) + (ENC ? 256 * 16 + (size_t)kSmallMaxItems * TOK * 2 : 0);
-    hipLaunchKernelGGL((rvq_small_kernel<D, ENC>), dim3((unsigned)nblk), dim3(Cfg<D>::THREADS), shm, stream,
+    const size_t shm = 2 * buf_bytes_of(Shape<D>::ROW_P, Kp) + (ENC ? 256 * 16 + (size_t)kSmallMaxItems * TOK * 2 : 0);
+    hipLaunchKernelGGL((rvq_small_kernel<D, ENC>), dim3((unsigned)nblk), dim3(Cfg<D, false>::THREADS), shm, stream,
                        (const _Float16*)x, (const _Float16*)books, stream_book, symbols, residual, n_bad, dsc->T,
                        dsc->t_begin, Ta, dsc->S, ns, dsc->K, Kp, dsc->n_books, bps, tpi, ipb, enc.points, enc.vtab, enc.r,
                        enc.N, enc.L, n_spans);
@@ -1232,7 +1326,7 @@ bool few_tokens(const fkv_rvq_desc* dsc, int ns, const GroupArgs& grp)
     const int64_t Ta = dsc->t_end - dsc->t_begin, n_items = grp.on ? grp.n_groups : dsc->n_streams;
     if (Ta > kFewTokens || (grp.on && grp.G * Ta > kFewTokens)) return false;
     if (!grp.on && D <= 64 && dsc->K <= kSmallK && ns <= 2) return false;
-    return n_items > 256 * Cfg<D>::MIN_BLOCKS || (D <= 64 && (grp.on ? grp.G : 1) * Ta <= 16);
+    return n_items > (D <= 64 ? 512 : 256) || (D <= 64 && (grp.on ? grp.G : 1) * Ta <= 16);
 }
 
 template <int D, bool GRP>
@@ -1249,44 +1343,48 @@ int launch_rvq_few(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uin
     return launch_status();
 }
 
+template <int D, bool WIDE>
+int launch_rvq_w(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint16_t* books,
+                 const int32_t* stream_book, uint8_t* symbols, float* residual, uint32_t* n_bad, const EncArgs& enc,
+                 const GroupArgs& grp, hipStream_t stream)
+{
+    if (grp.on)
+        return launch_rvq_t<D, WIDE, false, true>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,
+                                                        grp, stream);
+    if (enc.points)
+        return launch_rvq_t<D, WIDE, true, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,
+                                                        grp, stream);
+    return launch_rvq_t<D, WIDE, false, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,
+                                                     grp, stream);
+}
+
 template <int D>
 int launch_rvq(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint16_t* books,
                const int32_t* stream_book, uint8_t* symbols, float* residual, uint32_t* n_bad,
                const EncArgs& enc, const GroupArgs& grp, hipStream_t stream)
 {
-    // ns stages are assigned (the first ns of the S in the layout); the hi/lo
-    // residual is needed only from a third stage on
+    // ns stages are assigned (the first ns of the S in the layout)
     if (!enc.points && few_tokens<D>(dsc, ns, grp)) {
         if (grp.on)
             return launch_rvq_few<D, true>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, grp, stream);
         return launch_rvq_few<D, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, grp, stream);
     }
-    if (grp.on) {
-        if (ns <= 2)
-            return launch_rvq_t<D, false, false, true>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,
-                                                       grp, stream);
-        return launch_rvq_t<D, true, false, true>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, grp,
-                                                  stream);
-    }
     if constexpr (D <= 64) {
-        if (dsc->K <= kSmallK && ns <= 2) {
+        if (!grp.on && dsc->K <= kSmallK && ns <= 2) {
             if (enc.points)
                 return launch_rvq_small<D, true>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, stream);
             return launch_rvq_small<D, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, stream);
         }
     }
-    if (enc.points) {
-        if (ns <= 2)
-            return launch_rvq_t<D, false, true, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,
-                                                       grp, stream);
-        return launch_rvq_t<D, true, true, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, grp,
-                                                  stream);
+    if constexpr (D <= 128) {
+        const int64_t Ta = dsc->t_end - dsc->t_begin;
+        const int64_t items = (grp.on ? grp.n_groups : dsc->n_streams) *
+                              (((grp.on ? grp.G * Ta : Ta) + kItemTokens - 1) / kItemTokens);
+        if (items > 256)   // more than one item per compute unit
+            return launch_rvq_w<D, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, grp,
+                                                stream);
     }
-    if (ns <= 2)
-        return launch_rvq_t<D, false, false, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,
-                                                    grp, stream);
-    return launch_rvq_t<D, true, false, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, grp,
-                                               stream);
+    return launch_rvq_w<D, true>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, grp, stream);
 }
 
 int rvq_dispatch(const fkv_rvq_desc* desc, int ns, const uint16_t* x_f16, const uint16_t* books_f16,

@@ -103,6 +103,43 @@ def test_few_tokens_equal_bulk(fkv, d, S, K, n):
         assert (got[[1, 5]] == 0xFF).all() and np.isnan(gr[[1, 5]]).all()
 
 
+@pytest.mark.parametrize("d,S,K,n", [
+    (16, 2, 100, 40), (32, 1, 256, 257), (48, 3, 65, 130), (64, 2, 256, 300), (64, 4, 200, 65), (80, 3, 100, 255),
+    (96, 5, 129, 33), (112, 2, 256, 64), (128, 3, 256, 290), (128, 1, 70, 256), (128, 8, 256, 48),
+])
+def test_block_shapes_agree(fkv, d, S, K, n):
+    """Launches of more than 256 items take blocks of two token tiles per wave, smaller ones blocks of one:
+    symbols, residuals, points and counts are equal bit for bit, per stream, fused with the encode and grouped,
+    with ragged items, a padded book, equal codewords and a stream without a book."""
+    rng = np.random.default_rng(d + 3 * S + K + n)
+    nb, ns, t0 = 3, 280, 2
+    T = n + 5
+    x = (rng.standard_normal((ns, T, d)) * 2).astype(np.float16)
+    books = (rng.standard_normal((nb, S, K, d)) * (0.5 ** np.arange(S))[None, :, None, None]).astype(np.float16)
+    books[1, :, K - 1] = books[1, :, K // 2]
+    sb = rng.integers(0, nb, ns).astype(np.int32)
+    sb[7] = -1
+    xd, bd, sd = dev(x), dev(books), dev(sb)
+    nbad = torch.zeros(1, dtype=torch.int32, device="cuda")
+    sym, res = fkv.fkv_rvq_assign(xd, bd, sd, t0, t0 + n, want_residual=True, n_bad=nbad)
+    assert int(host(nbad)[0]) == 1
+    codec = fkv.Codec(256)
+    fs, fp, fr = fkv.fkv_rvq_assign_encode(codec, xd, bd, sd, t0, t0 + n, want_residual=True)
+    bits = lambda t: host(t).view(np.uint32)
+    assert torch.equal(fs, sym) and np.array_equal(bits(fr), bits(res))
+    some = slice(0, 100)                                # at most 200 items of 256 tokens
+    s1, r1 = fkv.fkv_rvq_assign(xd[some], bd, sd[some], t0, t0 + n, want_residual=True)
+    assert torch.equal(s1, sym[some]) and np.array_equal(bits(r1), bits(res[some]))
+    s2, p2, r2 = fkv.fkv_rvq_assign_encode(codec, xd[some], bd, sd[some], t0, t0 + n, want_residual=True)
+    assert torch.equal(s2, sym[some]) and np.array_equal(bits(r2), bits(res[some]))
+    assert np.array_equal(host(p2).view(np.uint64), host(fp[some]).view(np.uint64))
+    each = dev(np.delete(np.arange(ns, dtype=np.int32), 7)[:, None])
+    s3 = sym.clone()
+    s3[each[:, 0].long()] = 0x5A
+    fkv.fkv_rvq_assign_groups(xd, bd, sd, each, t0, t0 + n, symbols=s3)
+    assert torch.equal(s3, sym)
+
+
 def test_groups_invalid(fkv):
     rng = np.random.default_rng(3)
     d, S, K, T, nb, ns = 64, 2, 64, 20, 2, 6
