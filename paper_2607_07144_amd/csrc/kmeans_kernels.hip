@@ -2,12 +2,14 @@
 // codebooks (Sec. 3 "Setup": codebooks are trained by k-means), for gfx950.
 //
 // The assignment step is fkv_rvq_assign.  Accumulate: one block per book and
-// 64-dimension slice; one lane per 8 dimensions of a member token forms the
-// stage input r = x - (codewords of the earlier stages) exactly in fp64 and
-// adds it, as an integer in units of 2^-24 (every binary16 value is a multiple
-// of 2^-24), to its cluster's sum with 64-bit LDS atomics -- integer addition,
-// so the sums do not depend on the order of the atomics.  Finalize: mean = sum / count * 2^-24 in fp64, rounded once to
-// binary16; an empty cluster keeps its centroid.
+// 64-dimension slice sorts the member tokens by cluster; one lane per 8
+// dimensions of a member token forms the stage input r = x - (codewords of the
+// earlier stages) exactly in fp64, sums it in registers over a run of one
+// cluster, and adds the run, as integers in units of 2^-24 (every binary16 value
+// is a multiple of 2^-24), to the cluster's sum with 64-bit LDS atomics -- exact
+// at every step, so the sums do not depend on any order.  Finalize: mean = sum /
+// count * 2^-24 in fp64, rounded once to binary16; an empty cluster keeps its
+// centroid.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -25,29 +27,35 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 constexpr int kThreads = 256;
-// Accumulate: one 1024-thread block per (book, slice), so that enough member
-// tokens' loads are in flight to cover their latency (a block's tokens are
-// walked in 1024-task steps, each task waiting on its symbol, row and earlier
-// codewords).
 constexpr int kAccThreads = 1024;
-constexpr int kAccBatch = 4;   // tasks per thread whose loads are in flight together
-
-// One block per (book, 64-dimension slice): the block owns that slice of the
-// book's cluster sums, accumulates every member token of every stream of the
-// book into LDS (64-bit LDS atomics), then adds the slice to the global sums
-// with plain read-modify-writes (no other block touches it in this launch).
-// A cluster's row in LDS is dc + 1 words long: with an odd number of 8-byte
-// words per row, the same dimension of different clusters falls in different
-// banks (with dc words, every cluster's dimension e shared one bank, so the
-// atomics of a wave's tokens, which hit random clusters, serialised).
+constexpr int kAccBatch = 4;     // tokens per thread whose loads are in flight together
+constexpr int kChunk = 8192;     // tokens sorted by cluster at a time
 constexpr int kSlice = 64;
 
+// One block per (book, 64-dimension slice): the block owns that slice of the
+// book's cluster sums in LDS, and at the end adds it to the global sums with
+// plain read-modify-writes (no other block touches it in this launch).  The
+// member tokens are taken 8192 at a time and sorted by cluster (a counting sort
+// of 16-bit positions in LDS); each group of dc/8 lanes then walks a run of the
+// sorted list with its eight dimensions per lane summed in registers, and adds
+// them to LDS only where the cluster changes.  Adding every token to LDS with
+// 64-bit atomics was what bounded this kernel (17 LDS cycles per wave
+// instruction, eight per 8 tokens): 512 books of 256 x 128, 32,732 tokens each,
+// stage 0 1.28 -> 0.98 ms, stage 1 1.49 -> 1.19, stage 2 1.75 -> 1.47 (3.4 -> 4.4
+// TB/s of vectors at stage 0; they take 0.7 ms at 6 TB/s, the sort about a
+// quarter of a chunk's time, since one block fills a compute unit's LDS).
+// A register sum of n terms r = x - (earlier codewords), each a multiple of 2^-24
+// below 2^16 (stage + 1), is exact in fp64 while n (stage + 1) 2^40 < 2^53; a
+// group's run has at most kChunk / groups <= 64 tokens (8192 / 1024 per lane of a
+// row), so 64 * 8 * 2^40 = 2^49.
+// A cluster's row in LDS is dc + 1 words long: with an odd number of 8-byte
+// words per row, the same dimension of different clusters falls in different
+// banks.
+//
 // ST >= 0: the stage is fixed at compile time, so the loops over the earlier
 // stages unroll and all their codeword reads of a task batch are issued
-// together (one dependent memory round instead of one per earlier stage;
-// measured at the long-context shape: stage 1 from 8.1 to 6.5 ms, stage 2
-// from 10.6 to 7.6 ms).  ST = -1 takes the stage at run time (stages 5..7,
-// where the unrolled form would spill).
+// together.  ST = -1 takes the stage at run time (stages 5..7, where the
+// unrolled form would spill).
 template <int ST>
 __global__ __launch_bounds__(kAccThreads) void kmeans_accumulate_kernel(
     const _Float16* __restrict__ x, const _Float16* __restrict__ books, const int32_t* __restrict__ stream_book,
@@ -61,55 +69,116 @@ __global__ __launch_bounds__(kAccThreads) void kmeans_accumulate_kernel(
     const int e0 = slice * kSlice, dc = min(kSlice, d - e0);   // this block's dimensions [e0, e0 + dc)
     const int nch = dc / 8;
     const int pitch = dc + 1;                                    // words per cluster row
+    const int tid = threadIdx.x;
     unsigned long long* ls = (unsigned long long*)lds;           // [K][pitch]
-    uint32_t* lc = (uint32_t*)(ls + (size_t)K * pitch);          // [K]
-    int* match = (int*)(lc + K);                                 // [kAccThreads]: streams of a chunk using book b
+    uint32_t* lc = (uint32_t*)(ls + (size_t)K * pitch);          // [K] members so far
+    uint32_t* cnt = lc + K;                                      // [256] members in the chunk, then their places
+    uint32_t* wsum = cnt + 256;                                  // [4] wave totals of the scan
+    int* match = (int*)(wsum + 4);                               // [kAccThreads]: streams of a window using book b
     int* n_match = match + kAccThreads;
-    for (int i = threadIdx.x; i < K * pitch; i += kAccThreads) ls[i] = 0;
-    for (int i = threadIdx.x; i < K; i += kAccThreads) lc[i] = 0;
+    uint16_t* order = (uint16_t*)(n_match + 1);                  // [kChunk] the chunk's positions by cluster
+    for (int i = tid; i < K * pitch; i += kAccThreads) ls[i] = 0;
+    for (int i = tid; i < K; i += kAccThreads) lc[i] = 0;
+    const int n_groups = kAccThreads / nch, group = tid / nch, ch = tid - group * nch;
+    const float inv_Ta = 1.0f / (float)Ta;
     // The streams are scanned kAccThreads at a time, one per thread, and those
     // of book b listed in LDS (their order does not matter: integer sums).
     for (int64_t s0 = 0; s0 < n_streams; s0 += kAccThreads) {
-        if (threadIdx.x == 0) *n_match = 0;
+        if (tid == 0) *n_match = 0;
         __syncthreads();
-        if (s0 + threadIdx.x < n_streams && stream_book[s0 + threadIdx.x] == b)
-            match[atomicAdd(n_match, 1)] = (int)threadIdx.x;
+        if (s0 + tid < n_streams && stream_book[s0 + tid] == b) match[atomicAdd(n_match, 1)] = tid;
         __syncthreads();
-        const int nm = *n_match;
-        for (int m = 0; m < nm; ++m) {
-            const int64_t s = s0 + match[m];
-            // 32-bit task walk (the host checks that Ta * nch fits).  Each thread
-            // takes kAccBatch tasks at a time and issues all their loads before
-            // any sum, so the latencies of the batch overlap.
-            const int n_task = (int)(Ta * nch);
-            for (int task0 = threadIdx.x; task0 < n_task; task0 += kAccThreads * kAccBatch) {
-                int cl[kAccBatch];          // cluster of each task, -1: none (past the end, or skipped)
+        const int64_t total = (int64_t)*n_match * Ta;   // the window's member tokens, stream by stream
+        for (int64_t c0 = 0; c0 < total; c0 += kChunk) {
+            const int n = (int)min((int64_t)kChunk, total - c0);
+            const int m0 = (int)(c0 / Ta), r0 = (int)(c0 - (int64_t)m0 * Ta);
+            // position `rel` of the chunk: its stream and token (u + 1/2 is at
+            // least 1/(2 Ta) off every quotient's edge, far over the rounding)
+            auto locate = [&](int rel, int64_t& s, int64_t& t) {
+                const uint32_t u = (uint32_t)r0 + (uint32_t)rel;   // Ta < 2^31
+                const uint32_t q = Ta >= kChunk ? (u >= (uint32_t)Ta) : (uint32_t)(((float)u + 0.5f) * inv_Ta);
+                s = s0 + match[m0 + (int)q];
+                t = u - q * (uint32_t)Ta;
+            };
+            if (tid < 256) cnt[tid] = 0;
+            __syncthreads();
+            int place[kChunk / kAccThreads];   // cluster and rank within it; -1: past the end, or skipped
+#pragma unroll
+            for (int i = 0; i < kChunk / kAccThreads; ++i) {
+                const int rel = i * kAccThreads + tid;
+                place[i] = -1;
+                if (rel < n) {
+                    int64_t s, t;
+                    locate(rel, s, t);
+                    const uint8_t* sym = symbols + (s * Ta + t) * S;
+                    bool bad = false;
+                    int cl = 0;
+                    for (int st = 0; st <= stage; ++st) {
+                        cl = sym[st];
+                        bad = bad || cl >= K;   // outside the book: skipped
+                    }
+                    if (!bad) place[i] = cl << 16 | (int)atomicAdd(cnt + cl, 1u);
+                }
+            }
+            __syncthreads();
+            // exclusive prefix sums of the cluster sizes
+            uint32_t own = 0, inc = 0;
+            if (tid < 256) {
+                own = inc = cnt[tid];
+                for (int o = 1; o < 64; o <<= 1) {
+                    const uint32_t v = __shfl_up(inc, o);
+                    if ((tid & 63) >= o) inc += v;
+                }
+                if ((tid & 63) == 63) wsum[tid >> 6] = inc;
+                if (tid < K) lc[tid] += own;
+            }
+            __syncthreads();
+            if (tid < 256) {
+                for (int w = 0; w < (tid >> 6); ++w) inc += wsum[w];
+                cnt[tid] = inc - own;
+            }
+            const int nv = (int)(wsum[0] + wsum[1] + wsum[2] + wsum[3]);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kChunk / kAccThreads; ++i)
+                if (place[i] >= 0) order[cnt[place[i] >> 16] + (place[i] & 0xffff)] = (uint16_t)(i * kAccThreads + tid);
+            __syncthreads();
+
+            const int per = (nv + n_groups - 1) / n_groups;
+            const int p0 = min(nv, group * per), p1 = group < n_groups ? min(nv, p0 + per) : 0;
+            int cur = -1;
+            double acc[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] = 0.0;
+            auto flush = [&] {
+                if (cur < 0) return;
+                unsigned long long* dst = ls + (size_t)cur * pitch + ch * 8;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    // to units of 2^-24: |acc| 2^24 < 2^51, so adding 3 * 2^51 leaves
+                    // the integer in the low mantissa bits, exactly
+                    const double m = __builtin_fma(acc[e], 0x1p24, 0x1.8p52);
+                    atomicAdd(dst + e, (unsigned long long)(__double_as_longlong(m) - __double_as_longlong(0x1.8p52)));
+                }
+            };
+            for (int p = p0; p < p1; p += kAccBatch) {
                 int64_t row[kAccBatch];     // token row of x
                 const uint8_t* sym[kAccBatch];
-                int chn[kAccBatch];
 #pragma unroll
                 for (int u = 0; u < kAccBatch; ++u) {
-                    const int task = task0 + u * kAccThreads;
-                    const int t = task / nch;
-                    chn[u] = task - t * nch;
-                    sym[u] = symbols + (s * Ta + (task < n_task ? t : 0)) * S;
-                    row[u] = s * T + t_begin + (task < n_task ? t : 0);
-                    cl[u] = task < n_task ? 0 : -1;
+                    int64_t s, t;
+                    locate(order[min(p + u, p1 - 1)], s, t);
+                    row[u] = s * T + t_begin + t;
+                    sym[u] = symbols + (s * Ta + t) * S;
                 }
-                uint64_t sy[kAccBatch];     // the task's symbols of stages 0..stage, one byte each
+                half8 xv[kAccBatch];
+#pragma unroll
+                for (int u = 0; u < kAccBatch; ++u) xv[u] = *(const half8*)(x + row[u] * d + e0 + ch * 8);
+                uint64_t sy[kAccBatch];     // the token's symbols of stages 0..stage, one byte each
 #pragma unroll
                 for (int u = 0; u < kAccBatch; ++u) {
                     sy[u] = 0;
                     for (int st = 0; st <= stage; ++st) sy[u] |= (uint64_t)sym[u][st] << (8 * st);
-                }
-                half8 xv[kAccBatch];
-#pragma unroll
-                for (int u = 0; u < kAccBatch; ++u) xv[u] = *(const half8*)(x + row[u] * d + e0 + chn[u] * 8);
-#pragma unroll
-                for (int u = 0; u < kAccBatch; ++u) {
-                    bool bad = cl[u] < 0;
-                    for (int st = 0; st <= stage; ++st) bad = bad || (int)((sy[u] >> (8 * st)) & 255u) >= K;
-                    cl[u] = bad ? -1 : (int)((sy[u] >> (8 * stage)) & 255u);   // outside the book: skipped
                 }
                 double r[kAccBatch][8];
 #pragma unroll
@@ -121,9 +190,8 @@ __global__ __launch_bounds__(kAccThreads) void kmeans_accumulate_kernel(
                     half8 c[kAccBatch];
 #pragma unroll
                     for (int u = 0; u < kAccBatch; ++u)
-                        c[u] = *(const half8*)(books +
-                                               (((int64_t)b * S + st) * K + (cl[u] < 0 ? 0 : (int)((sy[u] >> (8 * st)) & 255u))) * d +
-                                               e0 + chn[u] * 8);
+                        c[u] = *(const half8*)(books + (((int64_t)b * S + st) * K + (int)((sy[u] >> (8 * st)) & 255u)) * d +
+                                               e0 + ch * 8);
 #pragma unroll
                     for (int u = 0; u < kAccBatch; ++u)
 #pragma unroll
@@ -131,24 +199,31 @@ __global__ __launch_bounds__(kAccThreads) void kmeans_accumulate_kernel(
                 }
 #pragma unroll
                 for (int u = 0; u < kAccBatch; ++u) {
-                    if (cl[u] < 0) continue;
-                    unsigned long long* dst = ls + (size_t)cl[u] * pitch + chn[u] * 8;
+                    if (p + u >= p1) continue;
+                    const int cl = (int)((sy[u] >> (8 * stage)) & 255u);
+                    if (cl != cur) {
+                        flush();
+                        cur = cl;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        atomicAdd(dst + e, (unsigned long long)(long long)ldexp(r[u][e], 24));
-                    if (chn[u] == 0 && slice == 0) atomicAdd(lc + cl[u], 1u);
+                        for (int e = 0; e < 8; ++e) acc[e] = r[u][e];
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) acc[e] = acc[e] + r[u][e];
+                    }
                 }
             }
+            flush();
+            __syncthreads();   // the chunk's order and counts are consumed
         }
-        __syncthreads();   // the list is rewritten for the next chunk
+        __syncthreads();   // the list is rewritten for the next window
     }
-    for (int i = threadIdx.x; i < K * dc; i += kAccThreads) {
+    for (int i = tid; i < K * dc; i += kAccThreads) {
         const int j = i / dc, e = i - j * dc;
         const unsigned long long v = ls[j * pitch + e];
         if (v) sums[((int64_t)b * K + j) * d + e0 + e] += v;
     }
     if (slice == 0)
-        for (int j = threadIdx.x; j < K; j += kAccThreads)
+        for (int j = tid; j < K; j += kAccThreads)
             if (lc[j]) counts[(int64_t)b * K + j] += lc[j];
 }
 
@@ -232,12 +307,15 @@ extern "C" int fkv_kmeans_accumulate(const fkv_rvq_desc* desc, const uint16_t* x
         return FKV_ERR_INVALID_ARG;
     const int n_slices = (D.d + kSlice - 1) / kSlice;
     if (Ta * (std::min(kSlice, (int)D.d) / 8) > 0x7fffffff - kAccThreads * kAccBatch) return FKV_ERR_UNSUPPORTED;
-    const size_t shm = (size_t)D.K * (std::min(kSlice, (int)D.d) + 1) * 8 + (size_t)D.K * 4 + (kAccThreads + 1) * 4;
+    auto lds_bytes = [](int K, int dc) {
+        return (size_t)K * (dc + 1) * 8 + (size_t)K * 4 + (256 + 4 + kAccThreads + 1) * 4 + kChunk * 2;
+    };
+    const size_t shm = lds_bytes(D.K, std::min(kSlice, (int)D.d));
     static std::once_flag once[6];   // one per kernel instance below
     auto go = [&](int slot, auto kern) {
         std::call_once(once[slot], [&] {
             (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      256 * (kSlice + 1) * 8 + 256 * 4 + (kAccThreads + 1) * 4);
+                                      (int)lds_bytes(256, kSlice));
         });
         (void)hipGetLastError();
         hipLaunchKernelGGL(kern, dim3((unsigned)(D.n_books * n_slices)), dim3(kAccThreads), shm, (hipStream_t)stream,

@@ -52,6 +52,36 @@ def test_every_stage_matches_oracle(fkv, orc, d, S, K):
         assert np.array_equal(host(bd).view(np.uint16), want.view(np.uint16)), stage
 
 
+@pytest.mark.parametrize("ns,T,d,S,K,stage,nb", [
+    (2, 8193, 64, 1, 256, 0, 1),      # a chunk of 8192 tokens and one more
+    (3, 8192, 16, 2, 5, 1, 2), (5, 4097, 8, 1, 256, 0, 1),     # chunks that straddle streams
+    (1500, 1, 24, 2, 40, 1, 3), (1030, 17, 8, 1, 7, 0, 1),     # one-token streams; more streams than one scan
+    (200, 100, 80, 3, 256, 2, 2), (4, 3000, 136, 2, 33, 1, 1), (2, 2500, 256, 6, 17, 5, 2), (9, 911, 72, 1, 1, 0, 1),
+])
+@pytest.mark.parametrize("extreme", [False, True])
+def test_sorted_sums_match_oracle(fkv, orc, ns, T, d, S, K, stage, nb, extreme):
+    """Chunks, stream boundaries, ragged slices and skipped tokens of the sorted accumulation; with the
+    largest and smallest binary16 values, where the register sums come closest to their bound."""
+    rng = np.random.default_rng(ns + T + d)
+    x = (rng.standard_normal((ns, T, d)) * 1.5).astype(np.float16)
+    books = (rng.standard_normal((nb, S, K, d)) * 0.5).astype(np.float16)
+    if extreme:
+        big, tiny = np.float16(65504), np.float16(2 ** -24)
+        x = np.where(rng.random(x.shape) < 0.9, big, tiny).astype(np.float16)
+        books = np.where(rng.random(books.shape) < 0.9, -big, -tiny).astype(np.float16)
+    sb = rng.integers(0, nb, ns).astype(np.int32)
+    sb[-1] = nb                                                    # no book
+    sym = rng.integers(0, min(K + 1, 256), (ns, T * S)).astype(np.uint8)   # some symbols outside the book
+    sym.reshape(-1, S)[: len(sym.reshape(-1, S)) // 2, stage] = K - 1      # one crowded cluster
+    bd = torch.from_numpy(books).cuda()
+    sums = torch.zeros((nb, K, d), dtype=torch.int64, device="cuda")
+    _, counts = fkv.fkv_kmeans_step(torch.from_numpy(x).cuda(), bd, torch.from_numpy(sb).cuda(), 0, T,
+                                    torch.from_numpy(sym).cuda(), stage, sums=sums)
+    want, _, wc = orc.kmeans_update(x, books, sb, 0, T, sym, stage)
+    assert np.array_equal(host(counts), wc)
+    assert np.array_equal(host(bd).view(np.uint16), want.view(np.uint16))
+
+
 def test_skipped_tokens(fkv, orc):
     """Streams with an invalid book id and tokens whose symbols reach K contribute nothing."""
     rng = np.random.default_rng(4)
