@@ -25,12 +25,14 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
 // ---------------------------------------------------------------- rehydrate --
 
-// A block takes QB queries at a time (64 while the grid has room for that
-// many blocks, else kBlock): its first QB threads look them up (one lane
-// each) into LDS, then all kBlock threads rebuild the output rows, up to
+// A block takes QB queries at a time: its first QB threads look them up (one
+// lane each) into LDS, then all kBlock threads rebuild the output rows, up to
 // kRehydU (query, 16-byte chunk) tasks per thread with their codebook-row
-// loads issued together, two stages at a time.
-constexpr int kRehydU = 2;
+// loads issued together, two stages at a time (four stages, or three: 98 and 90
+// registers instead of 82, a block fewer per compute unit and no faster).  What
+// bounds it is the chain of dependent reads: ids, point, codeword rows.
+constexpr int kRehydU = 2;   // tasks per thread
+constexpr int kRehydS = 2;   // stages whose loads are issued together
 
 template <int QB, bool EXACT>
 __global__ __launch_bounds__(kBlock) void rehydrate_kernel(
@@ -109,29 +111,27 @@ __global__ __launch_bounds__(kBlock) void rehydrate_kernel(
 #pragma unroll
                 for (int e = 0; e < 8; ++e) acc[u][e] = 0.0;
             }
-            // stages k and k + 1: every load first, then the sums in stage order
-            for (int k = 0; k < S; k += 2) {
-                half8 v0[kRehydU], v1[kRehydU];
+            // kRehydS stages at a time: every load first, then the sums in stage order
+            for (int k = 0; k < S; k += kRehydS) {
+                half8 v[kRehydU][kRehydS];
 #pragma unroll
                 for (int u = 0; u < kRehydU; ++u) {
-                    v0[u] = v1[u] = (half8)(_Float16)0;
-                    if (bb[u] >= 0) {
-                        const _Float16* row = books + ((int64_t)bb[u] * S + k) * K * d + ch[u] * 8;
-                        v0[u] = *(const half8*)(row + (int64_t)((sy[u] >> (8 * k)) & 0xff) * d);
-                        if (k + 1 < S)
-                            v1[u] = *(const half8*)(row + (int64_t)K * d +
-                                                    (int64_t)((sy[u] >> (8 * (k + 1))) & 0xff) * d);
+                    const _Float16* row = books + ((int64_t)bb[u] * S + k) * K * d + ch[u] * 8;
+#pragma unroll
+                    for (int j = 0; j < kRehydS; ++j) {
+                        v[u][j] = (half8)(_Float16)0;
+                        if (bb[u] >= 0 && k + j < S)
+                            v[u][j] = *(const half8*)(row + ((int64_t)j * K + (int64_t)((sy[u] >> (8 * (k + j))) & 0xff)) * d);
                     }
                 }
 #pragma unroll
-                for (int u = 0; u < kRehydU; ++u)
+                for (int j = 0; j < kRehydS; ++j) {
+                    if (k + j < S) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) acc[u][e] = acc[u][e] + (double)v0[u][e];
-                if (k + 1 < S) {
+                        for (int u = 0; u < kRehydU; ++u)
 #pragma unroll
-                    for (int u = 0; u < kRehydU; ++u)
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) acc[u][e] = acc[u][e] + (double)v1[u][e];
+                            for (int e = 0; e < 8; ++e) acc[u][e] = acc[u][e] + (double)v[u][j][e];
+                    }
                 }
             }
 #pragma unroll
@@ -369,8 +369,12 @@ extern "C" int fkv_rehydrate(const fkv_codec* c, const void* dev_table, const do
     if ((stream_book && !aligned(stream_book, 4)) || (n_failed && !aligned(n_failed, 4)))
         return FKV_ERR_INVALID_ARG;
     const int64_t n_spans = (n_sym + c->L - 1) / c->L;
-    const bool small_batches = (n_q + 63) / 64 <= kMaxBlocks;
-    const int qb = small_batches ? 64 : kBlock;
+    // 64 queries per block while the grid has room for that many blocks.  With
+    // rows of more than 128 bytes 64 queries are more than two tasks a thread,
+    // so up to four blocks per compute unit take 32 (one round of codeword
+    // loads).  Measured, 64 and 32 (us): d = 128, S = 3, 4000 queries 6.7 and 5.4,
+    // 32,768 10.1 and 9.5, 65,536 14.6 and 18.0; d = 64, S = 2, 16,000 5.1 and 5.5.
+    const int qb = d > 64 && n_q <= 32 * 1024 ? 32 : (n_q + 63) / 64 <= kMaxBlocks ? 64 : kBlock;
     const size_t shm =
         staged_table_bytes(c->N, false, needs_exact_sectors(c)) + (size_t)qb * (sizeof(int32_t) + sizeof(uint64_t));
     const int64_t nb = blocks_for((n_q + qb - 1) / qb);
@@ -381,10 +385,19 @@ extern "C" int fkv_rehydrate(const fkv_codec* c, const void* dev_table, const do
                            (const uint8_t*)dev_table, codec_args(c), n_streams, n_sym, n_spans, S, K, d, n_books,
                            n_q);
     };
+    auto pick = [&](auto exact) {
+        constexpr bool E = decltype(exact)::value;
+        if (qb == 32)
+            go(rehydrate_kernel<32, E>);
+        else if (qb == 64)
+            go(rehydrate_kernel<64, E>);
+        else
+            go(rehydrate_kernel<kBlock, E>);
+    };
     if (needs_exact_sectors(c))
-        small_batches ? go(rehydrate_kernel<64, true>) : go(rehydrate_kernel<kBlock, true>);
+        pick(std::true_type{});
     else
-        small_batches ? go(rehydrate_kernel<64, false>) : go(rehydrate_kernel<kBlock, false>);
+        pick(std::false_type{});
     return launch_status();
 }
 

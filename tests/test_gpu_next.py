@@ -86,6 +86,26 @@ def test_rehydrate_many_queries(fkv, orc, nq):
     assert (st == 2).sum() == len(set(range(0, nq, 997)) | set(range(5, nq, 1009))) and (st == 0).any()
 
 
+@pytest.mark.parametrize("d", [72, 128])
+@pytest.mark.parametrize("nq", [1, 32, 33, 32 * 1024, 32 * 1024 + 1])
+def test_rehydrate_wide_rows(fkv, orc, nq, d):
+    """Rows of more than 128 bytes on both sides of the switch from 32-query to 64-query batches."""
+    from dataclasses import replace
+    cfg = w.CONFIGS["tiny"]
+    cfg = replace(cfg, d=d) if d % 16 == 0 else replace(cfg, d=80)
+    x, books, sb, xd, bd, sd, sym, codec, pts = _gpu_archive(fkv, cfg)
+    if d % 16:                                          # a row length only rehydration takes
+        books = np.ascontiguousarray(books[..., :d])
+        bd = torch.from_numpy(books).cuda()
+    g = cfg.groups[0]
+    rng = np.random.default_rng(nq)
+    qs = rng.integers(0, x.shape[0], nq).astype(np.uint32)
+    qt = rng.integers(0, cfg.T_arch, nq).astype(np.uint32)
+    qs[3::101] = x.shape[0]
+    _, st = _check_rehydrate(fkv, orc, g, codec, pts, cfg.T_arch * g.S, books, sb, bd, sd, qs, qt)
+    assert (st == 2).sum() == len(range(3, nq, 101)) and (st[:3] == 0).all()
+
+
 def test_rehydrate_status_cases(fkv, orc):
     cfg = w.CONFIGS["tiny"]
     x, books, sb, xd, bd, sd, sym, codec, pts = _gpu_archive(fkv, cfg)
