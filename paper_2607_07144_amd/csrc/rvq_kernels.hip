@@ -37,7 +37,8 @@
 //
 // Codebooks.  Each stage's codebook is copied global -> LDS with the
 // asynchronous global_load_lds_dwordx4 into two alternating buffers, so the
-// next stage's book streams in while the current one is in use.  An LDS row
+// next stage's book streams in while the current one is in use (one buffer
+// where two or three blocks share a compute unit and cover each other's copies).  An LDS row
 // holds a codeword's 16-byte chunks followed by its bias-step chunk; the odd
 // chunk count per row spreads the 32 rows of an A fragment over distinct banks.
 #include <hip/hip_runtime.h>
@@ -1380,7 +1381,11 @@ int launch_rvq(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint16_
         const int64_t Ta = dsc->t_end - dsc->t_begin;
         const int64_t items = (grp.on ? grp.n_groups : dsc->n_streams) *
                               (((grp.on ? grp.G * Ta : Ta) + kItemTokens - 1) / kItemTokens);
-        if (items > 256)   // more than one item per compute unit
+        // more than one item per compute unit; at d <= 64 two wide blocks fit one,
+        // and with at most two stages their second book buffer wins up to 1536
+        // items (d = 64, S = 2, wide and narrow: 288 items 14.1 and 15.6 us, 1152 33.8
+        // and 35.5, 1536 45.2 and 45.4, 4608 117.9 and 116.4; S = 4, 512: 36.6 and 34.5)
+        if (items > (D <= 64 && ns <= 2 ? 1536 : 256))
             return launch_rvq_w<D, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, grp,
                                                 stream);
     }

@@ -108,11 +108,13 @@ def test_few_tokens_equal_bulk(fkv, d, S, K, n):
     (96, 5, 129, 33), (112, 2, 256, 64), (128, 3, 256, 290), (128, 1, 70, 256), (128, 8, 256, 48),
 ])
 def test_block_shapes_agree(fkv, d, S, K, n):
-    """Launches of more than 256 items take blocks of two token tiles per wave, smaller ones blocks of one:
+    """Large launches (more than 256 items; 1536 at d <= 64 with at most two stages) take blocks of two token
+    tiles per wave, smaller ones blocks of one:
     symbols, residuals, points and counts are equal bit for bit, per stream, fused with the encode and grouped,
     with ragged items, a padded book, equal codewords and a stream without a book."""
     rng = np.random.default_rng(d + 3 * S + K + n)
-    nb, ns, t0 = 3, 280, 2
+    nb, t0 = 3, 2
+    ns = 1560 if d <= 64 and S <= 2 else 280
     T = n + 5
     x = (rng.standard_normal((ns, T, d)) * 2).astype(np.float16)
     books = (rng.standard_normal((nb, S, K, d)) * (0.5 ** np.arange(S))[None, :, None, None]).astype(np.float16)
