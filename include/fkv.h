@@ -296,7 +296,9 @@ int fkv_suffix_search(const fkv_codec* c, const void* dev_table, const double* t
  *     sums[b][i_stage][0..d)   (device int64, units of 2^-24: exact integers)
  * and 1 to counts[b][i_stage] (device u32).  The caller zeroes both; desc is
  * read as for fkv_rvq_assign, except that d only has to be a multiple of 8
- * (8..256).  x, books: 16-byte aligned; sums 8-byte aligned.
+ * (8..256).  x, books: 16-byte aligned; sums 8-byte aligned.  An element of r
+ * that is NaN adds nothing to its sum, an infinite one 2^63 - 2^32 (positive)
+ * or -2^63 (negative), modulo 2^64; the token still counts.
  * fkv_kmeans_finalize replaces, for every cluster with count > 0, row
  * books[b][stage][j] by the mean sums / count * 2^-24 (fp64) rounded once to
  * binary16 (round to nearest, ties to even); an empty cluster keeps its

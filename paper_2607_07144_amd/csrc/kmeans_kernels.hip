@@ -32,6 +32,15 @@ constexpr int kAccBatch = 4;     // tokens per thread whose loads are in flight 
 constexpr int kChunk = 8192;     // tokens sorted by cluster at a time
 constexpr int kSlice = 64;
 
+// One element of a stage input in units of 2^-24.  A NaN adds nothing, and an
+// infinity the largest or smallest multiple of 2^32 that an int64 holds.
+__device__ __forceinline__ unsigned long long fixed24(double r)
+{
+    if (__builtin_isnan(r)) return 0;
+    if (__builtin_isinf(r)) return r > 0.0 ? 0x7FFFFFFF00000000ull : 0x8000000000000000ull;
+    return (unsigned long long)(long long)ldexp(r, 24);
+}
+
 // One block per (book, 64-dimension slice): the block owns that slice of the
 // book's cluster sums in LDS, and at the end adds it to the global sums with
 // plain read-modify-writes (no other block touches it in this launch).  The
@@ -48,6 +57,9 @@ constexpr int kSlice = 64;
 // below 2^16 (stage + 1), is exact in fp64 while n (stage + 1) 2^40 < 2^53; a
 // group's run has at most kChunk / groups <= 64 tokens (8192 / 1024 per lane of a
 // row), so 64 * 8 * 2^40 = 2^49.
+// A run that holds a NaN or an infinity (its register sum is not finite) is
+// walked again token by token instead, so that every finite element still counts
+// exactly and the sums still do not depend on any order.
 // A cluster's row in LDS is dc + 1 words long: with an odd number of 8-byte
 // words per row, the same dimension of different clusters falls in different
 // banks.
@@ -147,19 +159,30 @@ __global__ __launch_bounds__(kAccThreads) void kmeans_accumulate_kernel(
             const int per = (nv + n_groups - 1) / n_groups;
             const int p0 = min(nv, group * per), p1 = group < n_groups ? min(nv, p0 + per) : 0;
             int cur = -1;
+            bool again = false;   // a run was left out because its sum is not finite
             double acc[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[e] = 0.0;
             auto flush = [&] {
                 if (cur < 0) return;
                 unsigned long long* dst = ls + (size_t)cur * pitch + ch * 8;
+                // to units of 2^-24: |acc| 2^24 < 2^51, so adding 3 * 2^51 leaves the
+                // integer in the low mantissa bits, exactly, under the exponent of 2^52
+                // (all ones if acc is not finite)
+                long long m[8];
+                uint32_t top = 0;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    // to units of 2^-24: |acc| 2^24 < 2^51, so adding 3 * 2^51 leaves
-                    // the integer in the low mantissa bits, exactly
-                    const double m = __builtin_fma(acc[e], 0x1p24, 0x1.8p52);
-                    atomicAdd(dst + e, (unsigned long long)(__double_as_longlong(m) - __double_as_longlong(0x1.8p52)));
+                    m[e] = __double_as_longlong(__builtin_fma(acc[e], 0x1p24, 0x1.8p52));
+                    top = max(top, (uint32_t)(m[e] >> 32));
                 }
+                if (top >= 0x7FF00000u) {
+                    again = true;
+                    return;
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    atomicAdd(dst + e, (unsigned long long)(m[e] - __double_as_longlong(0x1.8p52)));
             };
             for (int p = p0; p < p1; p += kAccBatch) {
                 int64_t row[kAccBatch];     // token row of x
@@ -213,6 +236,38 @@ __global__ __launch_bounds__(kAccThreads) void kmeans_accumulate_kernel(
                 }
             }
             flush();
+            if (again) {
+                // the runs that hold a NaN or an infinity, token by token
+                auto cluster = [&](int q) {
+                    int64_t s, t;
+                    locate(order[q], s, t);
+                    return (int)symbols[(s * Ta + t) * S + stage];
+                };
+                auto element = [&](int q, int e) {
+                    int64_t s, t;
+                    locate(order[q], s, t);
+                    const uint8_t* sym = symbols + (s * Ta + t) * S;
+                    double r = (double)x[(s * T + t_begin + t) * d + e0 + ch * 8 + e];
+#pragma unroll 1
+                    for (int st = 0; st < stage; ++st)
+                        r = r - (double)books[(((int64_t)b * S + st) * K + sym[st]) * d + e0 + ch * 8 + e];
+                    return r;
+                };
+                int end;
+#pragma unroll 1
+                for (int p = p0; p < p1; p = end) {
+                    const int cl = cluster(p);
+                    bool finite = true;
+#pragma unroll 1
+                    for (end = p; end < p1 && cluster(end) == cl; ++end)
+#pragma unroll 1
+                        for (int e = 0; e < 8; ++e) finite = finite && __builtin_isfinite(element(end, e));
+                    if (finite) continue;   // counted already
+#pragma unroll 1
+                    for (int i = 0; i < 8 * (end - p); ++i)
+                        atomicAdd(ls + (size_t)cl * pitch + ch * 8 + (i & 7), fixed24(element(p + (i >> 3), i & 7)));
+                }
+            }
             __syncthreads();   // the chunk's order and counts are consumed
         }
         __syncthreads();   // the list is rewritten for the next window

@@ -82,6 +82,43 @@ def test_sorted_sums_match_oracle(fkv, orc, ns, T, d, S, K, stage, nb, extreme):
     assert np.array_equal(host(bd).view(np.uint16), want.view(np.uint16))
 
 
+@pytest.mark.parametrize("ns,T,d,S,K,stage", [
+    (3, 5000, 64, 1, 4, 0), (3, 900, 128, 3, 256, 2), (40, 30, 16, 6, 20, 5), (2, 700, 72, 5, 33, 4), (5, 37, 8, 1, 1, 0),
+])
+def test_non_finite_elements(fkv, ns, T, d, S, K, stage):
+    """A NaN element of a stage input adds nothing to its sum and an infinite one 2^63 - 2^32 or -2^63
+    (modulo 2^64); the finite elements of the same cluster, token and book still add up exactly, call after
+    call.  NaN and infinities come from the vectors and from the earlier stages' codewords."""
+    rng = np.random.default_rng(ns + T + d + S + K)
+    x = (rng.standard_normal((ns, T, d)) * 1.5).astype(np.float16)
+    books = (rng.standard_normal((2, S, K, d)) * 0.5).astype(np.float16)
+    for v in (np.nan, np.inf, -np.inf):
+        x[rng.integers(0, ns, 9), rng.integers(0, T, 9), rng.integers(0, d, 9)] = v
+        if stage:
+            books[rng.integers(0, 2, 3), rng.integers(0, stage, 3), rng.integers(0, K, 3), rng.integers(0, d, 3)] = v
+    sb = (np.arange(ns) % 2).astype(np.int32)
+    sym = rng.integers(0, K, (ns, T, S)).astype(np.uint8)
+    with np.errstate(invalid="ignore"):
+        r = x.astype(np.float64)
+        for st in range(stage):
+            r = r - books.astype(np.float64)[sb[:, None], st, sym[..., st]]
+    fixed = np.zeros(r.shape, np.int64)
+    fixed[np.isfinite(r)] = (r[np.isfinite(r)] * 2.0 ** 24).astype(np.int64)      # exact
+    fixed[r == np.inf] = 2 ** 63 - 2 ** 32
+    fixed[r == -np.inf] = -2 ** 63
+    want, wc = np.zeros((2, K, d), np.int64), np.zeros((2, K), np.int64)
+    where = (np.broadcast_to(sb[:, None], (ns, T)), sym[..., stage])
+    np.add.at(want, where, fixed)                                                  # wraps modulo 2^64
+    np.add.at(wc, where, 1)
+    assert np.isnan(r).any() and np.isinf(r).any()
+    for _ in range(3):
+        sums = torch.zeros((2, K, d), dtype=torch.int64, device="cuda")
+        _, counts = fkv.fkv_kmeans_step(torch.from_numpy(x).cuda(), torch.from_numpy(books).cuda(),
+                                        torch.from_numpy(sb).cuda(), 0, T, torch.from_numpy(sym).cuda().view(ns, T * S),
+                                        stage, sums=sums)
+        assert np.array_equal(host(counts), wc) and np.array_equal(host(sums), want)
+
+
 def test_skipped_tokens(fkv, orc):
     """Streams with an invalid book id and tokens whose symbols reach K contribute nothing."""
     rng = np.random.default_rng(4)
