@@ -7,12 +7,15 @@
 // earlier stages) exactly in fp64, sums it in registers over a run of one
 // cluster, and adds the run, as integers in units of 2^-24 (every binary16 value
 // is a multiple of 2^-24), to the cluster's sum with 64-bit LDS atomics -- exact
-// at every step, so the sums do not depend on any order.  Finalize: mean = sum /
+// at every step, so the sums do not depend on any order (few tokens, and narrow
+// rows, are added one by one without the sort).  Finalize: mean = sum /
 // count * 2^-24 in fp64, rounded once to binary16; an empty cluster keeps its
 // centroid.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include <algorithm>
 #include <mutex>
@@ -67,7 +70,10 @@ __device__ __forceinline__ unsigned long long fixed24(double r)
 // ST >= 0: the stage is fixed at compile time, so the loops over the earlier
 // stages unroll and all their codeword reads of a task batch are issued
 // together.  ST = -1 takes the stage at run time (stages 5..7, where the
-// unrolled form would spill).
+// unrolled form would spill).  B, the tokens whose loads are in flight together,
+// is what the registers hold (128 for 16 waves): with four, stages 3, 4 and 5.. keep
+// 16, 92 and 76 bytes of scratch.  512 books of 8192 tokens of 128, four, three and
+// two (us): stage 3 523, 536, 537; stage 4 649, 627, 638; stage 5 1358, 1373, 1152.
 template <int ST>
 __global__ __launch_bounds__(kAccThreads) void kmeans_accumulate_kernel(
     const _Float16* __restrict__ x, const _Float16* __restrict__ books, const int32_t* __restrict__ stream_book,
@@ -75,6 +81,7 @@ __global__ __launch_bounds__(kAccThreads) void kmeans_accumulate_kernel(
     int64_t n_streams, int64_t T, int64_t t_begin, int64_t Ta, int d, int S, int K, int stage_rt)
 {
     const int stage = ST >= 0 ? ST : stage_rt;
+    constexpr int B = ST == 4 ? 3 : ST < 0 ? 2 : kAccBatch;
     extern __shared__ __align__(16) uint8_t lds[];
     const int n_slices = (d + kSlice - 1) / kSlice;
     const int b = blockIdx.x / n_slices, slice = blockIdx.x - b * n_slices;
@@ -184,44 +191,44 @@ __global__ __launch_bounds__(kAccThreads) void kmeans_accumulate_kernel(
                 for (int e = 0; e < 8; ++e)
                     atomicAdd(dst + e, (unsigned long long)(m[e] - __double_as_longlong(0x1.8p52)));
             };
-            for (int p = p0; p < p1; p += kAccBatch) {
-                int64_t row[kAccBatch];     // token row of x
-                const uint8_t* sym[kAccBatch];
+            for (int p = p0; p < p1; p += B) {
+                int64_t row[B];     // token row of x
+                const uint8_t* sym[B];
 #pragma unroll
-                for (int u = 0; u < kAccBatch; ++u) {
+                for (int u = 0; u < B; ++u) {
                     int64_t s, t;
                     locate(order[min(p + u, p1 - 1)], s, t);
                     row[u] = s * T + t_begin + t;
                     sym[u] = symbols + (s * Ta + t) * S;
                 }
-                half8 xv[kAccBatch];
+                half8 xv[B];
 #pragma unroll
-                for (int u = 0; u < kAccBatch; ++u) xv[u] = *(const half8*)(x + row[u] * d + e0 + ch * 8);
-                uint64_t sy[kAccBatch];     // the token's symbols of stages 0..stage, one byte each
+                for (int u = 0; u < B; ++u) xv[u] = *(const half8*)(x + row[u] * d + e0 + ch * 8);
+                uint64_t sy[B];     // the token's symbols of stages 0..stage, one byte each
 #pragma unroll
-                for (int u = 0; u < kAccBatch; ++u) {
+                for (int u = 0; u < B; ++u) {
                     sy[u] = 0;
                     for (int st = 0; st <= stage; ++st) sy[u] |= (uint64_t)sym[u][st] << (8 * st);
                 }
-                double r[kAccBatch][8];
+                double r[B][8];
 #pragma unroll
-                for (int u = 0; u < kAccBatch; ++u)
+                for (int u = 0; u < B; ++u)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) r[u][e] = (double)xv[u][e];
 #pragma unroll
                 for (int st = 0; st < stage; ++st) {
-                    half8 c[kAccBatch];
+                    half8 c[B];
 #pragma unroll
-                    for (int u = 0; u < kAccBatch; ++u)
+                    for (int u = 0; u < B; ++u)
                         c[u] = *(const half8*)(books + (((int64_t)b * S + st) * K + (int)((sy[u] >> (8 * st)) & 255u)) * d +
                                                e0 + ch * 8);
 #pragma unroll
-                    for (int u = 0; u < kAccBatch; ++u)
+                    for (int u = 0; u < B; ++u)
 #pragma unroll
                         for (int e = 0; e < 8; ++e) r[u][e] = r[u][e] - (double)c[u][e];
                 }
 #pragma unroll
-                for (int u = 0; u < kAccBatch; ++u) {
+                for (int u = 0; u < B; ++u) {
                     if (p + u >= p1) continue;
                     const int cl = (int)((sy[u] >> (8 * stage)) & 255u);
                     if (cl != cur) {
@@ -279,6 +286,112 @@ __global__ __launch_bounds__(kAccThreads) void kmeans_accumulate_kernel(
     }
     if (slice == 0)
         for (int j = tid; j < K; j += kAccThreads)
+            if (lc[j]) counts[(int64_t)b * K + j] += lc[j];
+}
+
+// The same without the sort: stream by stream, each lane adds its eight elements
+// of every member token to LDS with 64-bit atomics.
+template <int ST>
+__global__ __launch_bounds__(kAccThreads) void kmeans_direct_kernel(
+    const _Float16* __restrict__ x, const _Float16* __restrict__ books, const int32_t* __restrict__ stream_book,
+    const uint8_t* __restrict__ symbols, unsigned long long* __restrict__ sums, uint32_t* __restrict__ counts,
+    int64_t n_streams, int64_t T, int64_t t_begin, int64_t Ta, int d, int S, int K, int stage_rt)
+{
+    const int stage = ST >= 0 ? ST : stage_rt;
+    extern __shared__ __align__(16) uint8_t lds[];
+    const int n_slices = (d + kSlice - 1) / kSlice;
+    const int b = blockIdx.x / n_slices, slice = blockIdx.x - b * n_slices;
+    const int e0 = slice * kSlice, dc = min(kSlice, d - e0);   // this block's dimensions [e0, e0 + dc)
+    const int nch = dc / 8;
+    const int pitch = dc + 1;                                    // words per cluster row
+    unsigned long long* ls = (unsigned long long*)lds;           // [K][pitch]
+    uint32_t* lc = (uint32_t*)(ls + (size_t)K * pitch);          // [K]
+    int* match = (int*)(lc + K);                                 // [kAccThreads]: streams of a chunk using book b
+    int* n_match = match + kAccThreads;
+    for (int i = threadIdx.x; i < K * pitch; i += kAccThreads) ls[i] = 0;
+    for (int i = threadIdx.x; i < K; i += kAccThreads) lc[i] = 0;
+    // The streams are scanned kAccThreads at a time, one per thread, and those
+    // of book b listed in LDS (their order does not matter: integer sums).
+    for (int64_t s0 = 0; s0 < n_streams; s0 += kAccThreads) {
+        if (threadIdx.x == 0) *n_match = 0;
+        __syncthreads();
+        if (s0 + threadIdx.x < n_streams && stream_book[s0 + threadIdx.x] == b)
+            match[atomicAdd(n_match, 1)] = (int)threadIdx.x;
+        __syncthreads();
+        const int nm = *n_match;
+        for (int m = 0; m < nm; ++m) {
+            const int64_t s = s0 + match[m];
+            // 32-bit task walk (the host checks that Ta * nch fits).  Each thread
+            // takes kAccBatch tasks at a time and issues all their loads before
+            // any sum, so the latencies of the batch overlap.
+            const int n_task = (int)(Ta * nch);
+            for (int task0 = threadIdx.x; task0 < n_task; task0 += kAccThreads * kAccBatch) {
+                int cl[kAccBatch];          // cluster of each task, -1: none (past the end, or skipped)
+                int64_t row[kAccBatch];     // token row of x
+                const uint8_t* sym[kAccBatch];
+                int chn[kAccBatch];
+#pragma unroll
+                for (int u = 0; u < kAccBatch; ++u) {
+                    const int task = task0 + u * kAccThreads;
+                    const int t = task / nch;
+                    chn[u] = task - t * nch;
+                    sym[u] = symbols + (s * Ta + (task < n_task ? t : 0)) * S;
+                    row[u] = s * T + t_begin + (task < n_task ? t : 0);
+                    cl[u] = task < n_task ? 0 : -1;
+                }
+                uint64_t sy[kAccBatch];     // the task's symbols of stages 0..stage, one byte each
+#pragma unroll
+                for (int u = 0; u < kAccBatch; ++u) {
+                    sy[u] = 0;
+                    for (int st = 0; st <= stage; ++st) sy[u] |= (uint64_t)sym[u][st] << (8 * st);
+                }
+                half8 xv[kAccBatch];
+#pragma unroll
+                for (int u = 0; u < kAccBatch; ++u) xv[u] = *(const half8*)(x + row[u] * d + e0 + chn[u] * 8);
+#pragma unroll
+                for (int u = 0; u < kAccBatch; ++u) {
+                    bool bad = cl[u] < 0;
+                    for (int st = 0; st <= stage; ++st) bad = bad || (int)((sy[u] >> (8 * st)) & 255u) >= K;
+                    cl[u] = bad ? -1 : (int)((sy[u] >> (8 * stage)) & 255u);   // outside the book: skipped
+                }
+                double r[kAccBatch][8];
+#pragma unroll
+                for (int u = 0; u < kAccBatch; ++u)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) r[u][e] = (double)xv[u][e];
+#pragma unroll
+                for (int st = 0; st < stage; ++st) {
+                    half8 c[kAccBatch];
+#pragma unroll
+                    for (int u = 0; u < kAccBatch; ++u)
+                        c[u] = *(const half8*)(books +
+                                               (((int64_t)b * S + st) * K + (cl[u] < 0 ? 0 : (int)((sy[u] >> (8 * st)) & 255u))) * d +
+                                               e0 + chn[u] * 8);
+#pragma unroll
+                    for (int u = 0; u < kAccBatch; ++u)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) r[u][e] = r[u][e] - (double)c[u][e];
+                }
+#pragma unroll
+                for (int u = 0; u < kAccBatch; ++u) {
+                    if (cl[u] < 0) continue;
+                    unsigned long long* dst = ls + (size_t)cl[u] * pitch + chn[u] * 8;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        atomicAdd(dst + e, (unsigned long long)(long long)ldexp(r[u][e], 24));   // NaN and infinities as fixed24
+                    if (chn[u] == 0 && slice == 0) atomicAdd(lc + cl[u], 1u);
+                }
+            }
+        }
+        __syncthreads();   // the list is rewritten for the next chunk
+    }
+    for (int i = threadIdx.x; i < K * dc; i += kAccThreads) {
+        const int j = i / dc, e = i - j * dc;
+        const unsigned long long v = ls[j * pitch + e];
+        if (v) sums[((int64_t)b * K + j) * d + e0 + e] += v;
+    }
+    if (slice == 0)
+        for (int j = threadIdx.x; j < K; j += kAccThreads)
             if (lc[j]) counts[(int64_t)b * K + j] += lc[j];
 }
 
@@ -362,15 +475,26 @@ extern "C" int fkv_kmeans_accumulate(const fkv_rvq_desc* desc, const uint16_t* x
         return FKV_ERR_INVALID_ARG;
     const int n_slices = (D.d + kSlice - 1) / kSlice;
     if (Ta * (std::min(kSlice, (int)D.d) / 8) > 0x7fffffff - kAccThreads * kAccBatch) return FKV_ERR_UNSUPPORTED;
-    auto lds_bytes = [](int K, int dc) {
-        return (size_t)K * (dc + 1) * 8 + (size_t)K * 4 + (256 + 4 + kAccThreads + 1) * 4 + kChunk * 2;
+    // The sort costs a chunk about 5 us of barriers, which few tokens do not repay,
+    // and the direct form pays 1.3 us per stream of a book.  A narrow row takes few
+    // lanes, so the atomics it saves are few, and two direct blocks fit a compute
+    // unit.  Measured, direct and sorted (us): one stream per book, K = 256: d = 64,
+    // 16 tokens 12.2 and 17.1, 300 tokens 25.5 and 30.0, 2500 tokens 68.1 and 58.3;
+    // d = 8, 4000 tokens 19.4 and 31.0; d = 48, 20,000 tokens in two streams 273 and
+    // 321.  200 books of 64 x 256: 4 streams of 64 tokens 18.7 and 19.0, 32 streams
+    // of 64 tokens 71.8 and 55.5.
+    const bool few = D.n_streams < 4 * (int64_t)D.n_books, narrow = D.d <= 24 || (D.d < 56 && D.n_books > 256);
+    const bool sort = narrow ? !few && Ta < 1024
+                             : !few || D.n_streams * Ta >= (int64_t)D.n_books * std::max(900, 8 * (int)D.K);
+    auto lds_bytes = [](int K, int dc, bool sort) {
+        return (size_t)K * (dc + 1) * 8 + (size_t)K * 4 + (kAccThreads + 1) * 4 + (sort ? (256 + 4) * 4 + kChunk * 2 : 0);
     };
-    const size_t shm = lds_bytes(D.K, std::min(kSlice, (int)D.d));
-    static std::once_flag once[6];   // one per kernel instance below
+    const size_t shm = lds_bytes(D.K, std::min(kSlice, (int)D.d), sort);
+    static std::once_flag once[12];   // one per kernel instance below
     auto go = [&](int slot, auto kern) {
         std::call_once(once[slot], [&] {
             (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (int)lds_bytes(256, kSlice));
+                                      (int)lds_bytes(256, kSlice, slot < 6));
         });
         (void)hipGetLastError();
         hipLaunchKernelGGL(kern, dim3((unsigned)(D.n_books * n_slices)), dim3(kAccThreads), shm, (hipStream_t)stream,
@@ -378,13 +502,17 @@ extern "C" int fkv_kmeans_accumulate(const fkv_rvq_desc* desc, const uint16_t* x
                            (unsigned long long*)sums, counts, D.n_streams, D.T, D.t_begin, Ta, D.d, D.S, D.K, stage);
         return launch_status();
     };
+    auto pick = [&](int slot, auto st) {
+        constexpr int ST = decltype(st)::value;
+        return sort ? go(slot, kmeans_accumulate_kernel<ST>) : go(6 + slot, kmeans_direct_kernel<ST>);
+    };
     switch (stage) {
-    case 0: return go(0, kmeans_accumulate_kernel<0>);
-    case 1: return go(1, kmeans_accumulate_kernel<1>);
-    case 2: return go(2, kmeans_accumulate_kernel<2>);
-    case 3: return go(3, kmeans_accumulate_kernel<3>);
-    case 4: return go(4, kmeans_accumulate_kernel<4>);
-    default: return go(5, kmeans_accumulate_kernel<-1>);
+    case 0: return pick(0, std::integral_constant<int, 0>{});
+    case 1: return pick(1, std::integral_constant<int, 1>{});
+    case 2: return pick(2, std::integral_constant<int, 2>{});
+    case 3: return pick(3, std::integral_constant<int, 3>{});
+    case 4: return pick(4, std::integral_constant<int, 4>{});
+    default: return pick(5, std::integral_constant<int, -1>{});
     }
 }
 

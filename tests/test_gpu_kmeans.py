@@ -82,6 +82,34 @@ def test_sorted_sums_match_oracle(fkv, orc, ns, T, d, S, K, stage, nb, extreme):
     assert np.array_equal(host(bd).view(np.uint16), want.view(np.uint16))
 
 
+@pytest.mark.parametrize("d,S,K,stage", [
+    (64, 2, 256, 1), (128, 3, 200, 2), (8, 1, 256, 0), (24, 8, 31, 7), (72, 5, 256, 4), (256, 4, 129, 3), (48, 6, 256, 5),
+])
+def test_direct_and_sorted_forms_agree(fkv, d, S, K, stage):
+    """The same 1500 tokens of each book as one stream (fewer tokens than the sort repays, or a narrow row: added
+    directly) and as six streams (sorted by cluster): sums and counts are equal bit for bit, with skipped
+    symbols and non-finite elements among them."""
+    rng = np.random.default_rng(d + S + K + stage)
+    nb, T = 260, 1500
+    x = (rng.standard_normal((nb, T, d)) * 1.5).astype(np.float16)
+    x[rng.integers(0, nb, 40), rng.integers(0, T, 40), rng.integers(0, d, 40)] = np.inf
+    x[rng.integers(0, nb, 40), rng.integers(0, T, 40), rng.integers(0, d, 40)] = np.nan
+    books = (rng.standard_normal((nb, S, K, d)) * 0.5).astype(np.float16)
+    sym = rng.integers(0, min(K + 1, 256), (nb, T * S)).astype(np.uint8)
+    sym[:, :S * 700] = K - 1
+    xd, sd = torch.from_numpy(x).cuda(), torch.from_numpy(sym).cuda()
+    got = []
+    for parts in (1, 6):
+        sb = torch.arange(nb, dtype=torch.int32, device="cuda").repeat_interleave(parts)
+        sums = torch.zeros((nb, K, d), dtype=torch.int64, device="cuda")
+        bd = torch.from_numpy(books).cuda()
+        _, counts = fkv.fkv_kmeans_step(xd.view(nb * parts, T // parts, d), bd, sb, 0, T // parts,
+                                        sd.view(nb * parts, -1), stage, sums=sums)
+        got.append((sums, counts, host(bd).view(np.uint16)))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert np.array_equal(got[0][2], got[1][2])
+
+
 @pytest.mark.parametrize("ns,T,d,S,K,stage", [
     (3, 5000, 64, 1, 4, 0), (3, 900, 128, 3, 256, 2), (40, 30, 16, 6, 20, 5), (2, 700, 72, 5, 33, 4), (5, 37, 8, 1, 1, 0),
 ])
