@@ -192,77 +192,98 @@ __global__ __launch_bounds__(kBlock) void append_kernel(double2* __restrict__ pt
 // candidate, kept when decoding ell symbols backward from it reproduces the
 // query.  The scan streams the index once (16 bytes per position).
 
-// A block takes one tile of U x 256 positions of a stream, in position order
-// over the grid: the blocks in flight then write one moving window of the
-// index.  (A persistent grid striding over 256-position tiles drifts apart and
-// writes at 4.5 TB/s whatever it computes; a kernel that only writes, one tile
-// per block, reaches 6.2-6.8 TB/s.)  At N = 256 it runs at 5.8 TB/s: beside the
-// writes, a wave needs six random 16-byte LDS reads per 64 positions.
+// Streams lie one after the other in symbols and index alike, so a block takes
+// one tile of U x 256 positions of them all, in position order over the grid:
+// the blocks in flight then write one moving window of the index, and tiles are
+// full whatever the streams' length.  (A persistent grid striding over
+// 256-position tiles drifts apart and writes at 4.5 TB/s whatever it computes; a
+// kernel that only writes, one tile per block, reaches 6.2-6.8 TB/s.)  Tiles that
+// began anew with each stream were slower than that persistent grid on short and
+// ragged streams.  Persistent, per-stream and these tiles (us): 100,000 streams of
+// 40, N = 256 79, 111 and 17; 4096 of 2049 36, 40 and 27; 10,000 of 3000, N = 16 208,
+// 186 and 159; 144 of 262,144, N = 256 141, 114 and 114 (5.6 TB/s), N = 64 212, 139 and 136,
+// N = 16 246, 197 and 192.
 template <int WC, int U>
-__global__ __launch_bounds__(kBlock, 8) void trajectory_kernel(const uint8_t* __restrict__ sym,
-                                                                double2* __restrict__ traj,
-                                                                const uint8_t* __restrict__ gtab, CodecArgs cd,
-                                                                int64_t n_sym, int W, int64_t tiles_per_stream,
-                                                                int64_t n_tiles)
+__global__ __launch_bounds__(kBlock) void trajectory_kernel(
+    const uint8_t* __restrict__ sym, double2* __restrict__ traj, const uint8_t* __restrict__ gtab, CodecArgs cd,
+    int64_t n_sym, float inv_n, int W, int64_t n_pos)
 {
     constexpr int TILE = U * kBlock;
     extern __shared__ __align__(16) uint8_t lds[];
     const int N = cd.N, tid = threadIdx.x;
     double2* V = (double2*)lds;
-    uint8_t* tile = lds + 256 * sizeof(double2);
+    uint8_t* tile = lds + 256 * sizeof(double2) + 64;   // a window that reaches back past position 0 reads 64 bytes before
+    const int64_t k0 = (int64_t)blockIdx.x * TILE;
+    const int nk = (int)min((int64_t)TILE, n_pos - k0);
+    const int64_t g0 = max((int64_t)0, k0 - W + 1);
     const double2 vreg = tid < N ? ((const double2*)(gtab + table_off_V(N)))[tid] : make_double2(NAN, NAN);
-    bool staged = false;
-    for (int64_t tl = blockIdx.x; tl < n_tiles; tl += gridDim.x) {
-        // a 64-bit division is emulated
-        const int64_t s = n_tiles <= 0x7fffffff ? (int64_t)((uint32_t)tl / (uint32_t)tiles_per_stream) : tl / tiles_per_stream;
-        const int64_t k0 = (tl - s * tiles_per_stream) * TILE;
-        const int64_t a0 = max((int64_t)0, k0 - W + 1);
-        const int nk = (int)min((int64_t)TILE, n_sym - k0);
-        const int h = (int)(k0 - a0);   // symbols of history before the tile
-        const int64_t g0 = s * n_sym + a0, g1 = s * n_sym + k0 + nk;
-        if (staged) __syncthreads();   // previous tile consumed
-        bytes_to_lds(sym, g0, g1, tile);
-        if (!staged) V[tid] = vreg;
-        staged = true;
-        __syncthreads();
-        const int base = (int)(g0 & 3) + h;   // LDS offset of position k0's own symbol
-        double2* out = traj + s * n_sym + k0;
-        // the full window ending at k0 + k: its bytes from the aligned LDS
-        // dwords that cover them, then the walk
-        auto walk = [&](int k) {
-            constexpr int NE = WC > 0 ? (WC + 3) / 4 : 1;
-            const int off = base + k + 1 - WC;
-            const uint32_t* t32 = (const uint32_t*)tile + (off >> 2);
-            uint32_t dw[NE + 1], e[NE];
-#pragma unroll
-            for (int q = 0; q <= NE; ++q) dw[q] = t32[q];
-#pragma unroll
-            for (int q = 0; q < NE; ++q) e[q] = __builtin_amdgcn_alignbyte(dw[q + 1], dw[q], off);
-            double2 v[WC > 0 ? WC : 1];
-#pragma unroll
-            for (int j = 0; j < WC; ++j) v[j] = V[(e[j >> 2] >> (8 * (j & 3))) & 0xFF];
-            double px = 0.0, py = 0.0;
-#pragma unroll
-            for (int j = 0; j < WC; ++j) encode_step(px, py, v[j], cd.r);
-            store_point_stream(out + k, px, py);
-        };
-        if (WC > 0 && nk == TILE && h == WC - 1) {
-            // whole tile, every window full: no predicate, so the walks interleave
-#pragma unroll
-            for (int u = 0; u < U; ++u) walk(u * kBlock + tid);
-        } else {
-            for (int k = tid; k < nk; k += kBlock) {
-                if (WC > 0 && h + k + 1 >= WC) {
-                    walk(k);
-                    continue;
-                }
-                const int len = min(WC > 0 ? WC : W, h + k + 1);
-                const uint8_t* my = tile + base + k + 1 - len;
-                double px = 0.0, py = 0.0;
-                for (int j = 0; j < len; ++j) encode_step(px, py, V[my[j]], cd.r);
-                store_point_stream(out + k, px, py);
-            }
+    bytes_to_lds(sym, g0, k0 + nk, tile);
+    V[tid] = vreg;
+    __syncthreads();
+    const int base = (int)(g0 & 3) + (int)(k0 - g0);   // LDS offset of position k0's own symbol
+    // position k0's place in its stream (a 64-bit division is emulated)
+    const int64_t r0 = n_pos <= 0x7fffffff ? (int64_t)((uint32_t)k0 % (uint32_t)n_sym) : k0 % n_sym;
+    double2* out = traj + k0;
+    // Symbols of the stream up to position k0 + k, counted no further than a
+    // window needs.  A tile holds at most one stream's start (at position `next`),
+    // unless streams are shorter than it: then the place is a remainder, by a
+    // reciprocal (u + 1/2 is at least 1/(2 n_sym) off every quotient's edge, u < 4096).
+    const bool shorter = n_sym < TILE;
+    const int first = shorter ? (int)r0 : (int)min(r0, (int64_t)64);
+    const int next = shorter ? 0 : (int)min(n_sym - r0, (int64_t)TILE);
+    auto history = [&](int k) {
+        if (shorter) {
+            const uint32_t u = (uint32_t)(first + k);
+            return (int)(u - (uint32_t)(((float)u + 0.5f) * inv_n) * (uint32_t)n_sym) + 1;
         }
+        return (k < next ? first + k : k - next) + 1;
+    };
+    // the window ending at k0 + k: its bytes from the aligned LDS dwords that
+    // cover them, then the walk of its last `len` symbols (WHOLE: all of them)
+    auto walk = [&](int k, int len, auto whole) {
+        constexpr bool WHOLE = decltype(whole)::value;
+        constexpr int NE = WC > 0 ? (WC + 3) / 4 : 1;
+        const int off = base + k + 1 - WC;
+        const uint32_t* t32 = (const uint32_t*)(tile + (off & ~3));
+        uint32_t dw[NE + 1], e[NE];
+#pragma unroll
+        for (int q = 0; q <= NE; ++q) dw[q] = t32[q];
+#pragma unroll
+        for (int q = 0; q < NE; ++q) e[q] = __builtin_amdgcn_alignbyte(dw[q + 1], dw[q], off);
+        double2 v[WC > 0 ? WC : 1];
+#pragma unroll
+        for (int j = 0; j < WC; ++j) v[j] = V[(e[j >> 2] >> (8 * (j & 3))) & 0xFF];
+        double px = 0.0, py = 0.0;
+#pragma unroll
+        for (int j = 0; j < WC; ++j) {
+            double qx = px, qy = py;
+            encode_step(qx, qy, v[j], cd.r);
+            px = WHOLE || j >= WC - len ? qx : px;
+            py = WHOLE || j >= WC - len ? qy : py;
+        }
+        store_point_stream(out + k, px, py);
+    };
+    if (WC > 0 && nk == TILE && r0 >= WC - 1 && n_sym - r0 >= TILE) {
+        // whole tile, every window full: no predicate, so the walks interleave
+#pragma unroll
+        for (int u = 0; u < U; ++u) walk(u * kBlock + tid, WC, std::true_type{});
+        return;
+    }
+    for (int k = tid; k < nk; k += kBlock) {
+        const int len = min(WC > 0 ? WC : W, history(k));
+        if (WC > 0 && __all(len == WC)) {
+            walk(k, WC, std::true_type{});
+            continue;
+        }
+        if constexpr (WC > 0 && WC <= 9) {   // 16 predicates more would spill
+            walk(k, len, std::false_type{});
+            continue;
+        }
+        const uint8_t* my = tile + base + k + 1 - len;
+        double px = 0.0, py = 0.0;
+#pragma unroll 4
+        for (int j = 0; j < len; ++j) encode_step(px, py, V[my[j]], cd.r);
+        store_point_stream(out + k, px, py);
     }
 }
 
@@ -425,36 +446,31 @@ extern "C" int fkv_trajectory(const fkv_codec* c, const void* dev_table, const u
     if (!symbols || !traj || !aligned(symbols, 4) || !aligned(traj, 16) || !aligned(dev_table, 16))
         return FKV_ERR_INVALID_ARG;
     // the codec's own span length L is the usual window: 6, 9 and 16 for N = 256, 64 and 16
+    const int64_t n_pos = n_streams * n_sym;
     auto go = [&](auto kern, int tile) {
-        const int64_t tps = (n_sym + tile - 1) / tile;
-        const int64_t n_tiles = tps * n_streams;
-        const size_t shm = 256 * 16 + (size_t)tile + 64 + 16;
-        hipLaunchKernelGGL(kern, dim3((unsigned)min(n_tiles, kMaxTileBlocks)), dim3(kBlock), shm, (hipStream_t)stream,
-                           symbols, (double2*)traj, (const uint8_t*)dev_table, codec_args(c), n_sym, W, tps, n_tiles);
+        const int64_t n_tiles = (n_pos + tile - 1) / tile;
+        if (n_tiles > 0xffffff) return (int)FKV_ERR_UNSUPPORTED;   // 2^24 blocks of 256 threads: an index of 550 GB
+        const size_t shm = 256 * 16 + 64 + (size_t)tile + 64 + 16;
+        hipLaunchKernelGGL(kern, dim3((unsigned)n_tiles), dim3(kBlock), shm, (hipStream_t)stream, symbols,
+                           (double2*)traj, (const uint8_t*)dev_table, codec_args(c), n_sym, 1.0f / (float)n_sym, W,
+                           n_pos);
+        return launch_status();
     };
     auto pick = [&](auto u) {
         constexpr int U = decltype(u)::value;
-        if (W == 6)
-            go(trajectory_kernel<6, U>, U * kBlock);
-        else if (W == 9)
-            go(trajectory_kernel<9, U>, U * kBlock);
-        else if (W == 16)
-            go(trajectory_kernel<16, U>, U * kBlock);
-        else
-            go(trajectory_kernel<0, U>, U * kBlock);
+        if (W == 6) return go(trajectory_kernel<6, U>, U * kBlock);
+        if (W == 9) return go(trajectory_kernel<9, U>, U * kBlock);
+        if (W == 16) return go(trajectory_kernel<16, U>, U * kBlock);
+        return go(trajectory_kernel<0, U>, U * kBlock);
     };
-    // Tiles of 2048 positions once they give every compute unit two blocks,
-    // else of 256, so that a small index still spreads over the chip (kernel
-    // time differs by less than a launch there).  Measured with 256- and
-    // 2048-position tiles: 37.7 M positions 166 and 110 us (the persistent
-    // 256-position form this replaced 135 us: 4.7 -> 5.8 TB/s), 4.0 M 21.5 and
-    // 17.8 us, 0.9 M 10.9 and 11.2 us.
-    const bool big = n_streams * ((n_sym + 8 * kBlock - 1) / (8 * kBlock)) >= 512;
-    if (big)
-        pick(std::integral_constant<int, 8>{});
-    else
-        pick(std::integral_constant<int, 1>{});
-    return launch_status();
+    // Tiles of 2048 positions once nearly two of them reach every compute unit
+    // (eight, where the window's length is not known at compile time and a block
+    // walks it step by step), else of 256, so that a small index still spreads over the
+    // chip.  Measured with 256- and 2048-position tiles (us): 37.7 M positions, W = 6 179
+    // and 114; 1.02 M, W = 6 7.0 and 5.7, W = 16 9.9 and 9.2, W = 20 11.0 and 17.6; 0.5 M, W = 6
+    // 5.0 and 5.1, W = 16 7.3 and 13.1; 2.1 M, W = 20 19.8 and 23.6.
+    const bool big = n_pos >= (W == 6 || W == 9 || W == 16 ? 448 : 2048) * 8 * kBlock;
+    return big ? pick(std::integral_constant<int, 8>{}) : pick(std::integral_constant<int, 1>{});
 }
 
 extern "C" int fkv_suffix_search(const fkv_codec* c, const void* dev_table, const double* traj, int64_t n_streams,

@@ -24,7 +24,6 @@ namespace {
 
 constexpr int kBlock = 256;        // threads per block = spans per tile
 constexpr int kMaxBlocks = 2048;   // persistent grid cap (8 blocks per CU)
-constexpr int64_t kMaxTileBlocks = 1 << 22;   // grid cap where a block takes one tile
 
 struct CodecArgs {
     int N;

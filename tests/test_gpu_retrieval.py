@@ -50,14 +50,35 @@ def test_trajectory_short_streams(fkv, orc, n_sym, W):
 @pytest.mark.parametrize("ns,n_sym,N,W", [(512, 37, 256, 6), (512, 3, 256, 6), (257, 2049, 256, 6), (171, 4100, 64, 9),
                                           (256, 2051, 16, 16), (130, 6145, 256, 7), (512, 2047, 3, 64)])
 def test_trajectory_large_tiles(fkv, orc, ns, n_sym, N, W):
-    """Indexes of at least 512 tiles of 2048 positions: whole tiles, one-position remainders, streams shorter
-    than a tile or the window, odd stream lengths (every byte alignment), symbols outside the alphabet."""
+    """Streams around the length of a 2048-position tile, shorter than a tile or the window, odd stream lengths
+    (every byte alignment), symbols outside the alphabet."""
     rng = np.random.default_rng(ns + n_sym)
     sym = rng.integers(0, N, (ns, n_sym), dtype=np.uint8)
     want = orc.trajectory(orc.Codec(N), sym, W)
     if N < 256:
         sym[1, n_sym // 2] = N          # NaN points while it is in the window
         want[1, n_sym // 2:n_sym // 2 + W] = np.nan
+    tr = host(fkv.fkv_trajectory(fkv.Codec(N), torch.from_numpy(sym).cuda(), W))
+    bad = np.isnan(want)
+    assert np.array_equal(np.isnan(tr), bad)
+    assert np.array_equal(tr.view(np.uint64)[~bad], want.view(np.uint64)[~bad])
+
+
+@pytest.mark.parametrize("ns,n_sym,N,W", [
+    (171, 5400, 16, 16), (171, 5400, 64, 9),              # tiles without, with and next to a stream's start
+    (400000, 3, 256, 6), (100003, 17, 16, 16), (24001, 40, 64, 9), (1000003, 1, 256, 6),   # many starts per tile
+    (4490, 2047, 256, 6), (4600, 2049, 64, 9), (449, 2048, 16, 16),                        # around the tile's length
+    (66000, 70, 256, 64), (1000, 9, 256, 64), (3, 255, 16, 16), (5, 257, 64, 9), (90, 31, 16, 16),   # long windows, small tiles
+])
+def test_trajectory_tiles_cross_streams(fkv, orc, ns, n_sym, N, W):
+    """Tiles run over the streams as they lie: short windows at every place of a tile, 256- and 2048-position
+    tiles, a symbol outside the alphabet at a stream's end (the next stream's windows do not hold it)."""
+    rng = np.random.default_rng(ns + 3 * n_sym + N)
+    sym = rng.integers(0, N, (ns, n_sym), dtype=np.uint8)
+    want = orc.trajectory(orc.Codec(N), sym, W)
+    if N < 256:
+        sym[ns // 2, -1] = N
+        want[ns // 2, -1] = np.nan
     tr = host(fkv.fkv_trajectory(fkv.Codec(N), torch.from_numpy(sym).cuda(), W))
     bad = np.isnan(want)
     assert np.array_equal(np.isnan(tr), bad)
