@@ -447,10 +447,10 @@ __device__ __forceinline__ void resplit2(uint32_t a, uint32_t b, uint32_t c, uin
 // + e] is member e of group g) and its tokens are the members' archived
 // tokens, member by member, so that one block serves all of them with a single
 // copy of the book (the per-token arithmetic is that of the per-stream form).
-template <int D, bool WIDE, bool ENC, bool GRP>
-constexpr bool kPers = WIDE && D > 128 && !ENC && !GRP;
-
-template <int D, bool WIDE, bool ENC, bool GRP>
+// PERS: a block takes ipb consecutive work items (token ranges, mostly of one
+// stream) and loads the next item's token rows into registers during the current
+// item's last stage, so a new item does not start by waiting on HBM.
+template <int D, bool WIDE, bool ENC, bool GRP, bool PERS>
 __global__ __launch_bounds__((Cfg<D, WIDE>::THREADS), (Cfg<D, WIDE>::BLOCKS)) void rvq_assign_kernel(
     const _Float16* __restrict__ x, const _Float16* __restrict__ books,
     const int32_t* __restrict__ stream_book, uint8_t* __restrict__ symbols,
@@ -461,11 +461,6 @@ __global__ __launch_bounds__((Cfg<D, WIDE>::THREADS), (Cfg<D, WIDE>::BLOCKS)) vo
 {
     static_assert(!(GRP && ENC), "the grouped form has no fused encode");
     using C = Cfg<D, WIDE>;
-    // PERS: a block takes ipb consecutive work items (token ranges, mostly of
-    // one stream) and loads the next item's token rows into registers during
-    // the current item's last stage, so a new item does not start by waiting
-    // on HBM.  (In the narrow shape the other block's scans cover that wait.)
-    constexpr bool PERS = kPers<D, WIDE, ENC, GRP>;
     constexpr int KS = C::KS, TT = C::TT, NBUF = C::NBUF;
     extern __shared__ __align__(16) uint8_t lds[];
     // LDS: NBUF buffers of Kp rows (codeword + bias-step chunk) and a zero
@@ -1228,7 +1223,7 @@ struct GroupArgs {
     int G;
 };
 
-template <int D, bool WIDE, bool ENC, bool GRP>
+template <int D, bool WIDE, bool ENC, bool GRP, bool PERS>
 int launch_rvq_t(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint16_t* books,
                  const int32_t* stream_book, uint8_t* symbols, float* residual, uint32_t* n_bad,
                  const EncArgs& enc, const GroupArgs& grp, hipStream_t stream)
@@ -1236,7 +1231,7 @@ int launch_rvq_t(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint1
     static std::once_flag once;
     const int Kp = (dsc->K + 63) / 64 * 64;  // whole pairs of 32-codeword tiles
     std::call_once(once, [] {
-        (void)hipFuncSetAttribute((const void*)rvq_assign_kernel<D, WIDE, ENC, GRP>,
+        (void)hipFuncSetAttribute((const void*)rvq_assign_kernel<D, WIDE, ENC, GRP, PERS>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)(lds_bytes<D, WIDE>(256) + (ENC ? enc_lds_bytes() : 0)));
     });
@@ -1260,12 +1255,12 @@ int launch_rvq_t(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint1
     const int64_t n_items = bps * items;
     // 16 items per block once there are at least 64 blocks' worth per compute
     // unit
-    const int64_t ipb = (kPers<D, WIDE, ENC, GRP> && ns > 2 && n_items >= 256 * 64) ? 16 : 1;
+    const int64_t ipb = (PERS && ns > 2 && n_items >= 256 * 64) ? 16 : 1;
     const int64_t nblk = (n_items + ipb - 1) / ipb;
     if (nblk > 0x7fffffff) return FKV_ERR_UNSUPPORTED;
     const int64_t n_spans = ENC ? (Ta * dsc->S + enc.L - 1) / enc.L : 0;
     const size_t shm = lds_bytes<D, WIDE>(Kp) + (ENC ? enc_lds_bytes() : 0);
-    hipLaunchKernelGGL((rvq_assign_kernel<D, WIDE, ENC, GRP>), dim3((unsigned)nblk), dim3(Cfg<D, WIDE>::THREADS), shm,
+    hipLaunchKernelGGL((rvq_assign_kernel<D, WIDE, ENC, GRP, PERS>), dim3((unsigned)nblk), dim3(Cfg<D, WIDE>::THREADS), shm,
                        stream, (const _Float16*)x, (const _Float16*)books, stream_book, symbols, residual, n_bad,
                        dsc->T, dsc->t_begin, Ta, dsc->S, ns, dsc->K, Kp, dsc->n_books, bps, tpb, enc.points, enc.vtab,
                        enc.r, enc.N, enc.L, n_spans, grp.groups, grp.G, dsc->n_streams, ipb, n_items);
@@ -1350,13 +1345,23 @@ int launch_rvq_w(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint1
                  const GroupArgs& grp, hipStream_t stream)
 {
     if (grp.on)
-        return launch_rvq_t<D, WIDE, false, true>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,
-                                                        grp, stream);
+        return launch_rvq_t<D, WIDE, false, true, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,
+                                                         grp, stream);
     if (enc.points)
-        return launch_rvq_t<D, WIDE, true, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,
-                                                        grp, stream);
-    return launch_rvq_t<D, WIDE, false, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,
-                                                     grp, stream);
+        return launch_rvq_t<D, WIDE, true, false, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc,
+                                                         grp, stream);
+    // Blocks that can take several items, above d = 128 (in the narrow shape the
+    // other block's scans cover an item's first wait).  With at most two stages the
+    // prefetched rows only cost registers.  Without and with them (us), K = 256: d =
+    // 256, 600 streams of 512, S = 1 71 and 109; 1000 of 988, S = 2 544 and 595; S = 4,
+    // K = 200, 600 of 300 341 and 327; d = 192, S = 1 55 and 72.  (At d = 208 the form
+    // without them spills inside the scan: S = 2 781 and 470.)
+    if constexpr (WIDE && D > 128)
+        if (ns > 2 || (D == 208 && ns == 2))
+            return launch_rvq_t<D, WIDE, false, false, true>(dsc, ns, x, books, stream_book, symbols, residual, n_bad,
+                                                             enc, grp, stream);
+    return launch_rvq_t<D, WIDE, false, false, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, grp,
+                                                      stream);
 }
 
 template <int D>

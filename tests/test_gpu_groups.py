@@ -201,12 +201,13 @@ def test_eviction_step_matches_oracle(fkv, orc):
 
 
 def test_multi_item_blocks_match_single_item_blocks(fkv):
-    """At 2^14 and more work items the hi/lo per-stream form gives each block 16 consecutive items and
-    loads the next item's rows during the current item's last stage; the grouped form (one stream per
-    group) keeps one item per block with the same arithmetic.  Symbols, residuals and the invalid-stream
-    count must agree, with invalid streams between valid ones (an item that ends a block's run early)."""
+    """At 2^14 and more work items, three or more stages and d > 128 the per-stream form gives each block 16
+    consecutive items and loads the next item's rows during the current item's last stage; the grouped form
+    (one stream per group) keeps one item per block with the same arithmetic.  Symbols, residuals and the
+    invalid-stream count must agree, with invalid streams between valid ones (an item that ends a block's run
+    early)."""
     rng = np.random.default_rng(11)
-    ns, T, d, S, K, nb = 128, 32800, 128, 3, 64, 4
+    ns, T, d, S, K, nb = 128, 32800, 144, 3, 64, 4
     t0, t1 = 4, 32772                                   # 32,768 tokens: 128 items of 256 per stream
     x = torch.from_numpy((rng.standard_normal((ns, T, d)) * 1.2).astype(np.float16)).cuda()
     books = torch.from_numpy((rng.standard_normal((nb, S, K, d)) *
@@ -226,3 +227,47 @@ def test_multi_item_blocks_match_single_item_blocks(fkv):
     assert np.array_equal(np.nan_to_num(a).view(np.uint32), np.nan_to_num(b).view(np.uint32))
     del x, s1, s2, r1, r2
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("d,S,K,ns,n", [(144, 3, 100, 16403, 33), (256, 4, 256, 16401, 35), (208, 3, 70, 8210, 300)])
+def test_multi_item_blocks_of_short_streams(fkv, d, S, K, ns, n):
+    """The same with blocks that cross from stream to stream (one ragged item, or a whole and a ragged one, per
+    stream), an item count that 16 does not divide and streams without a book inside a block's run, against
+    calls of few streams, which give each block one item."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + n)
+    nb, T, t0 = 5, n + 2, 1
+    x = torch.randn((ns, T, d), generator=g, device="cuda").half()
+    scale = 0.5 ** torch.arange(S, device="cuda")
+    books = (torch.randn((nb, S, K, d), generator=g, device="cuda") * scale[None, :, None, None]).half()
+    sb = (torch.arange(ns, device="cuda") * 7 % nb).int()
+    sb[[0, 18, 19, 5000, ns - 1]] = nb
+    nbad = torch.zeros(1, dtype=torch.int32, device="cuda")
+    sym, res = fkv.fkv_rvq_assign(x, books, sb, t0, t0 + n, want_residual=True, n_bad=nbad)
+    assert int(host(nbad)[0]) == 5
+    for a in range(0, ns, 4096):
+        s1, r1 = fkv.fkv_rvq_assign(x[a:a + 4096], books, sb[a:a + 4096], t0, t0 + n, want_residual=True)
+        assert torch.equal(s1, sym[a:a + 4096])
+        assert torch.equal(r1.view(torch.int32), res[a:a + 4096].view(torch.int32))
+
+
+@pytest.mark.parametrize("d", [144, 160, 192, 208, 240, 256])
+def test_first_stages_of_wide_heads(fkv, d):
+    """Above d = 128, calls of one or two stages run blocks without the next item's rows, deeper ones with them:
+    the first stages' symbols are the same."""
+    rng = np.random.default_rng(d)
+    ns, T, S, K, nb = 7, 300, 3, 200, 3
+    x = (rng.standard_normal((ns, T, d)) * 2).astype(np.float16)
+    books = (rng.standard_normal((nb, S, K, d)) * (0.5 ** np.arange(S))[None, :, None, None]).astype(np.float16)
+    sb = rng.integers(0, nb, ns).astype(np.int32)
+    xd, bd, sd = dev(x), dev(books), dev(sb)
+    full = host(fkv.fkv_rvq_assign(xd, bd, sd, 0, T)[0]).reshape(ns, T, S)
+    for k in (1, 2):
+        sym = torch.full((ns, T * S), 0xA5, dtype=torch.uint8, device="cuda")
+        _, res = fkv.fkv_rvq_assign(xd, bd, sd, 0, T, symbols=sym, n_stages=k, want_residual=True)
+        got = host(sym).reshape(ns, T, S)
+        assert np.array_equal(got[..., :k], full[..., :k]) and (got[..., k:] == 0xA5).all()
+        r = x.astype(np.float64)
+        for st in range(k):
+            r = r - books.astype(np.float64)[sb[:, None], st, full[..., st]]
+        assert np.abs(host(res) - r).max() <= 1e-3
