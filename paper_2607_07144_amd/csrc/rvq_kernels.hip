@@ -1306,23 +1306,78 @@ int launch_rvq_small(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const u
     return launch_status();
 }
 
+// Whether two wide blocks fit a compute unit: 16 waves' registers (at most 128 each
+// up to d = 80) and two pairs of book buffers.
+template <int D>
+bool two_wide(const fkv_rvq_desc* dsc)
+{
+    return D <= 80 && 2 * lds_bytes<D, true>((dsc->K + 63) / 64 * 64) <= kLdsBudget;
+}
+
 // Whether a call of at most 32 tokens per work item takes rvq_few_kernel.  It
 // does once there are more items than the staged form has resident blocks (one
 // or two per compute unit): that form then runs them in rounds.  Below that,
 // the staged form starts all its copies at once and only loses at d <= 64,
-// where its two-tile waves scan 64 columns for a few tokens.  Measured, staged
+// where it scans 64 columns for a few tokens.  Measured, staged
 // and few (us): d = 128, S = 3, K = 256, 512 items of 4 tokens 36.0 and 21.4,
 // 300 of 16 31.7 and 22.3, 144 of 16 13.6 and 14.9; 2048 streams of 32 tokens
 // 160 and 79.  d = 64, S = 2, K = 256, 288 items of 1 token 7.0 and 6.1, 144 of
 // 16 9.9 and 8.5, 300 of 32 11.7 and 13.1.  Small books keep their own kernel
 // in the per-stream form (K = 64, 2304 streams of 32 tokens: 14.0 and 15.8).
+//
+// A small book gives a block few waves, which then split many tokens' residuals
+// between them (from a third stage on, chunk by chunk): there the staged form is
+// the faster one up to about two rounds of its blocks, the more so where a wave
+// without tokens skips its scan (groups) or two wide blocks fit a compute unit.
+// Staged and few (us), groups: d = 80, S = 3, 300 items: K = 64, 32 tokens 7.9 and
+// 13.6, 8 tokens 7.9 and 8.5, K = 256, 32 tokens 18.6 and 15.6; d = 128, S = 4, K = 32,
+// 300 items of 32 20.0 and 28.2; d = 192, S = 4, K = 32, 1500 of 32 86 and 117; d = 16,
+// S = 4, K = 32, 600 of 32 8.5 and 12.3.  One stage of a large book has no second load
+// to overlap either: d = 192, S = 1, K = 192, 300 items 10.4 and 12.7.
 template <int D>
 bool few_tokens(const fkv_rvq_desc* dsc, int ns, const GroupArgs& grp)
 {
     const int64_t Ta = dsc->t_end - dsc->t_begin, n_items = grp.on ? grp.n_groups : dsc->n_streams;
     if (Ta > kFewTokens || (grp.on && grp.G * Ta > kFewTokens)) return false;
-    if (!grp.on && D <= 64 && dsc->K <= kSmallK && ns <= 2) return false;
-    return n_items > (D <= 64 ? 512 : 256) || (D <= 64 && (grp.on ? grp.G : 1) * Ta <= 16);
+    const int K = dsc->K;
+    const int64_t tokens = (grp.on ? grp.G : 1) * Ta;
+    if (!grp.on && D <= 64 && K <= kSmallK && ns <= 2) return false;
+    if (n_items <= (D <= 64 ? 512 : 256) && (D > 64 || tokens > 16)) return false;
+    if (ns >= 3 && tokens > 16) {
+        if (grp.on && D <= 32 && n_items <= 1024) return false;
+        if (K <= 64 && (grp.on ? D <= 208 && n_items <= 1024 : D <= 144 && n_items <= 512)) return false;
+    }
+    if (!grp.on) return true;
+    if (D == 80 && two_wide<D>(dsc) && tokens > (ns >= 3 && n_items <= 512 ? 8 : 16) && (ns >= 3 || n_items <= 512))
+        return false;
+    if (D <= 64 && ns >= 3 && tokens > 8 && K <= 64 && n_items <= 1024) return false;
+    if (D <= 208 && ns == 2 && tokens > 16 && K <= 64 && n_items <= 512) return false;
+    if (D > 128 && D <= 208 && ns >= 3 && tokens > 16 && K <= 32) return false;
+    return !(ns == 1 && K > 128 && (D <= 64 ? n_items <= 512 : D > 128 && D <= 208 && (n_items <= 512 || tokens >= 16)));
+}
+
+// Whether the staged form's blocks are narrow (d <= 128): with more than one full
+// item per compute unit they are.  At d <= 64 two wide blocks fit one, and with at
+// most two stages their second book buffer wins up to 1536 items (d = 64, S = 2,
+// wide and narrow: 288 items 14.1 and 15.6 us, 1152 33.8 and 35.5, 1536 45.2 and 45.4,
+// 4608 117.9 and 116.4; S = 4, 512: 36.6 and 34.5).  Items of at most half a block's
+// tokens leave half of a narrow block's waves idle, while the wide shape's
+// eight all have a tile, and copy the books twice as fast: S = 4, K = 256, wide and
+// narrow (us): d = 64, 300 items of 128 tokens 18.5 and 28.9; d = 128, 300 of 128 44.7 and
+// 50.9, 1600 of 128 162 and 175; S = 3, 2500 of 64 192 and 185.  At d = 80 two wide
+// blocks fit a compute unit up to K = 192, and only full items make up for one book
+// buffer: S = 3, K = 128, 1600 items of 128 tokens 46 and 64, of 200 68 and 73.
+template <int D>
+bool narrow_blocks(const fkv_rvq_desc* dsc, int ns, const GroupArgs& grp)
+{
+    if (D > 128) return false;
+    const int64_t Ta = dsc->t_end - dsc->t_begin, units = grp.on ? grp.n_groups : dsc->n_streams;
+    const int64_t tokens = grp.on ? grp.G * Ta : Ta, per_unit = (tokens + kItemTokens - 1) / kItemTokens;
+    const int64_t items = units * per_unit;
+    if (D <= 64) return items > (ns <= 2 ? 1536 : tokens > 200 * per_unit ? 256 : 512);
+    if (D == 80 && two_wide<D>(dsc)) return items > 256 && tokens > 240 * per_unit;
+    if (2 * tokens <= kItemTokens && (ns >= 4 ? items <= 2048 : ns == 3 && items <= 1024)) return false;
+    return items > 256;
 }
 
 template <int D, bool GRP>
@@ -1382,18 +1437,9 @@ int launch_rvq(const fkv_rvq_desc* dsc, int ns, const uint16_t* x, const uint16_
             return launch_rvq_small<D, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, stream);
         }
     }
-    if constexpr (D <= 128) {
-        const int64_t Ta = dsc->t_end - dsc->t_begin;
-        const int64_t items = (grp.on ? grp.n_groups : dsc->n_streams) *
-                              (((grp.on ? grp.G * Ta : Ta) + kItemTokens - 1) / kItemTokens);
-        // more than one item per compute unit; at d <= 64 two wide blocks fit one,
-        // and with at most two stages their second book buffer wins up to 1536
-        // items (d = 64, S = 2, wide and narrow: 288 items 14.1 and 15.6 us, 1152 33.8
-        // and 35.5, 1536 45.2 and 45.4, 4608 117.9 and 116.4; S = 4, 512: 36.6 and 34.5)
-        if (items > (D <= 64 && ns <= 2 ? 1536 : 256))
-            return launch_rvq_w<D, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, grp,
-                                                stream);
-    }
+    if constexpr (D <= 128)
+        if (narrow_blocks<D>(dsc, ns, grp))
+            return launch_rvq_w<D, false>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, grp, stream);
     return launch_rvq_w<D, true>(dsc, ns, x, books, stream_book, symbols, residual, n_bad, enc, grp, stream);
 }
 

@@ -106,10 +106,11 @@ def test_few_tokens_equal_bulk(fkv, d, S, K, n):
 @pytest.mark.parametrize("d,S,K,n", [
     (16, 2, 100, 40), (32, 1, 256, 257), (48, 3, 65, 130), (64, 2, 256, 300), (64, 4, 200, 65), (80, 3, 100, 255),
     (96, 5, 129, 33), (112, 2, 256, 64), (128, 3, 256, 290), (128, 1, 70, 256), (128, 8, 256, 48),
+    (48, 3, 65, 210), (64, 4, 200, 201), (96, 5, 129, 133), (128, 8, 256, 150), (80, 3, 100, 200), (80, 2, 256, 130),
 ])
 def test_block_shapes_agree(fkv, d, S, K, n):
-    """Large launches (more than 256 items; 1536 at d <= 64 with at most two stages) take blocks of two token
-    tiles per wave, smaller ones blocks of one:
+    """Large launches of full enough items (more than 256; 1536 at d <= 64 with at most two stages) take blocks
+    of two token tiles per wave, smaller ones, and deep ones of half-empty items, blocks of one:
     symbols, residuals, points and counts are equal bit for bit, per stream, fused with the encode and grouped,
     with ragged items, a padded book, equal codewords and a stream without a book."""
     rng = np.random.default_rng(d + 3 * S + K + n)
@@ -271,3 +272,79 @@ def test_first_stages_of_wide_heads(fkv, d):
         for st in range(k):
             r = r - books.astype(np.float64)[sb[:, None], st, full[..., st]]
         assert np.abs(host(res) - r).max() <= 1e-3
+
+
+@pytest.mark.parametrize("d,S,K,G,n,ng", [
+    (128, 3, 130, 3, 75, 270), (128, 2, 256, 4, 100, 140), (96, 4, 256, 5, 45, 300), (80, 3, 256, 4, 37, 280),
+    (112, 1, 33, 3, 50, 300), (64, 2, 256, 5, 45, 1540), (64, 4, 200, 3, 83, 280), (16, 3, 100, 3, 77, 300),
+])
+def test_large_grouped_launches(fkv, d, S, K, G, n, ng):
+    """Grouped launches of more items than the wide shape's limits: two token tiles per wave, members that end
+    inside a tile (n is not a multiple of 32) and items that hold several members or, at 4 x 100 tokens, split
+    them, against the per-stream form a few streams at a time."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + n)
+    ns, nb, T, t0 = ng * G, 9, n + 3, 2
+    x = torch.randn((ns, T, d), generator=g, device="cuda").half()
+    scale = 0.5 ** torch.arange(S, device="cuda")
+    books = (torch.randn((nb, S, K, d), generator=g, device="cuda") * scale[None, :, None, None]).half()
+    groups = torch.randperm(ns, generator=g, device="cuda").int().view(ng, G)
+    sb = torch.empty(ns, dtype=torch.int32, device="cuda")
+    sb[groups.long()] = (torch.arange(ng, device="cuda") % nb).int()[:, None]
+    bad = groups[11].long()
+    sb[bad] = nb                                        # a group without a book
+    nbad = torch.zeros(1, dtype=torch.int32, device="cuda")
+    sym, res = fkv.fkv_rvq_assign_groups(x, books, sb, groups, t0, t0 + n, want_residual=True, n_bad=nbad)
+    assert int(host(nbad)[0]) == 1 and bool((sym[bad] == 0xFF).all())
+    for a in range(0, ns, 200):
+        s1, r1 = fkv.fkv_rvq_assign(x[a:a + 200], books, sb[a:a + 200], t0, t0 + n, want_residual=True)
+        assert torch.equal(s1, sym[a:a + 200])
+        assert torch.equal(r1.view(torch.int32), res[a:a + 200].view(torch.int32))
+
+
+def test_few_tokens_more_items_than_blocks(fkv):
+    """More work items than the few-token kernel has blocks (2^20): a block takes a second item, after one with a
+    book and after one without."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    ns, d, S, K, nb = (1 << 20) + 37, 16, 3, 100, 7
+    x = torch.randn((ns, 1, d), generator=g, device="cuda").half()
+    books = torch.randn((nb, S, K, d), generator=g, device="cuda").half()
+    sb = torch.randint(0, nb, (ns,), generator=g, device="cuda", dtype=torch.int32)
+    sb[[3, 9, (1 << 20) + 9, (1 << 20) + 12, ns - 1]] = -1
+    nbad = torch.zeros(1, dtype=torch.int32, device="cuda")
+    sym, res = fkv.fkv_rvq_assign(x, books, sb, 0, 1, want_residual=True, n_bad=nbad)
+    assert int(host(nbad)[0]) == 5
+    groups = torch.arange(ns, device="cuda", dtype=torch.int32)[:, None].contiguous()
+    nbad.zero_()
+    s2, r2 = fkv.fkv_rvq_assign_groups(x, books, sb, groups, 0, 1, want_residual=True, n_bad=nbad)
+    assert int(host(nbad)[0]) == 5
+    assert torch.equal(s2, sym) and torch.equal(r2.view(torch.int32), res.view(torch.int32))
+    for a in range(0, ns, 1 << 18):
+        s1, r1 = fkv.fkv_rvq_assign(x[a:a + (1 << 18)], books, sb[a:a + (1 << 18)], 0, 1, want_residual=True)
+        assert torch.equal(s1, sym[a:a + (1 << 18)])
+        assert torch.equal(r1.view(torch.int32), res[a:a + (1 << 18)].view(torch.int32))
+
+
+@pytest.mark.parametrize("d,S,K,G,n,ng", [
+    (16, 3, 100, 1, 32, 600), (16, 3, 64, 3, 4, 100), (64, 3, 64, 4, 4, 100), (64, 1, 192, 2, 1, 300), (64, 4, 33, 2, 5, 600),
+    (80, 3, 192, 3, 6, 300), (80, 3, 64, 4, 2, 300), (80, 2, 100, 2, 16, 400), (96, 2, 64, 1, 32, 300), (128, 4, 40, 2, 16, 300),
+    (192, 1, 200, 4, 8, 300), (192, 3, 32, 1, 30, 300), (208, 2, 64, 2, 15, 280), (256, 3, 64, 1, 32, 300),
+])
+def test_few_tokens_of_small_books(fkv, d, S, K, G, n, ng):
+    """Calls of at most 32 tokens per group on both sides of the choice between the few-token kernel and the
+    staged form (small books, many tokens, one stage), against the staged form over a longer range."""
+    rng = np.random.default_rng(d + 5 * S + K + n)
+    ns, nb, t0 = ng * G, 4, 3
+    T = max(n + 5, 38)
+    x = (rng.standard_normal((ns, T, d)) * 2).astype(np.float16)
+    books = (rng.standard_normal((nb, S, K, d)) * (0.5 ** np.arange(S))[None, :, None, None]).astype(np.float16)
+    sb = np.repeat(rng.integers(0, nb, ng), G).astype(np.int32)
+    xd, bd, sd = dev(x), dev(books), dev(sb)
+    full, fres = fkv.fkv_rvq_assign(xd, bd, sd, 0, T, want_residual=True)
+    full, fres = host(full).reshape(ns, T, S)[:, t0:t0 + n], host(fres)[:, t0:t0 + n]
+    groups = dev(np.arange(ns, dtype=np.int32).reshape(ng, G))
+    for sym, res in (fkv.fkv_rvq_assign(xd, bd, sd, t0, t0 + n, want_residual=True),
+                     fkv.fkv_rvq_assign_groups(xd, bd, sd, groups, t0, t0 + n, want_residual=True)):
+        assert np.array_equal(host(sym).reshape(ns, n, S), full)
+        assert np.array_equal(host(res).view(np.uint32), fres.view(np.uint32))
