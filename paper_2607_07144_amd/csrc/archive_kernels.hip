@@ -29,8 +29,9 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 // lane each) into LDS, then all kBlock threads rebuild the output rows, up to
 // kRehydU (query, 16-byte chunk) tasks per thread with their codebook-row
 // loads issued together, two stages at a time (four stages, or three: 98 and 90
-// registers instead of 82, a block fewer per compute unit and no faster).  What
-// bounds it is the chain of dependent reads: ids, point, codeword rows.
+// registers instead of 82, no faster; registers come in steps of 8, so 82 and 90
+// leave five blocks per compute unit, 98 four, and the 256-query instance's 80 six).
+// What bounds it is the chain of dependent reads: ids, point, codeword rows.
 constexpr int kRehydU = 2;   // tasks per thread
 constexpr int kRehydS = 2;   // stages whose loads are issued together
 
@@ -201,8 +202,10 @@ __global__ __launch_bounds__(kBlock) void append_kernel(double2* __restrict__ pt
 // began anew with each stream were slower than that persistent grid on short and
 // ragged streams.  Persistent, per-stream and these tiles (us): 100,000 streams of
 // 40, N = 256 79, 111 and 17; 4096 of 2049 36, 40 and 27; 10,000 of 3000, N = 16 208,
-// 186 and 159; 144 of 262,144, N = 256 141, 114 and 114 (5.6 TB/s), N = 64 212, 139 and 136,
-// N = 16 246, 197 and 192.
+// 186 and 159; 144 of 262,144, N = 256 141, 114 and 113 (5.7 TB/s), N = 64 212, 139
+// and 136, N = 16 246, 197 and 192.  What bounds it is LDS: busy 88% of a compute
+// unit's cycles at W = 6, 59% of that bank conflicts of the six random 16-byte
+// vertex reads per position; the vector ALU is busy 68%.
 template <int WC, int U>
 __global__ __launch_bounds__(kBlock) void trajectory_kernel(
     const uint8_t* __restrict__ sym, double2* __restrict__ traj, const uint8_t* __restrict__ gtab, CodecArgs cd,

@@ -236,26 +236,17 @@ __device__ __forceinline__ void load_frag(Frag<D>& f, const uint8_t* buf, uint32
     f.bias = *(const half8*)(tile + Shape<D>::NCH * 16);
 }
 
-// acc[tt] = bias step + A(tile) x B(tt) over all k-steps; with TWO a second B
-// operand accumulates into the same tile.
-template <int D, int TT, bool TWO>
-__device__ __forceinline__ void issue_tile(const Frag<D>& f, const half8 (&bz)[TT],
-                                           const half8 (&bA)[TT][Shape<D>::KS],
-                                           const half8 (&bB)[TT][Shape<D>::KS], floatx16 (&acc)[TT])
+// acc = bias step + A(tile) x B over all k-steps; with TWO a second B operand
+// accumulates into the same tile.
+template <int D, bool TWO>
+__device__ __forceinline__ void issue_tile(const Frag<D>& f, const half8& bz, const half8 (&bA)[Shape<D>::KS],
+                                           const half8 (&bB)[Shape<D>::KS], floatx16& acc)
 {
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt)
-        acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.bias, bz[tt], (floatx16)0.0f, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.bias, bz, (floatx16)0.0f, 0, 0, 0);
 #pragma unroll
     for (int ks = 0; ks < Shape<D>::KS; ++ks) {
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt)
-            acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.a[ks], bA[tt][ks], acc[tt], 0, 0, 0);
-        if (TWO) {
-#pragma unroll
-            for (int tt = 0; tt < TT; ++tt)
-                acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.a[ks], bB[tt][ks], acc[tt], 0, 0, 0);
-        }
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.a[ks], bA[ks], acc, 0, 0, 0);
+        if (TWO) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.a[ks], bB[ks], acc, 0, 0, 0);
     }
 }
 
@@ -277,27 +268,15 @@ __device__ __forceinline__ uint32_t tile_min_key(const floatx16& a)
     return min(m5, m6);
 }
 
-// Key minimum of the first tile of a pair (positions 0..15).
-template <int TT>
-__device__ __forceinline__ void pair_first(const floatx16 (&acc)[TT], uint32_t (&pk)[TT])
+// Adds the scores of the second tile of pair `pair` (positions 16..31) to the key
+// minimum pk of its first tile (positions 0..15) and folds the pair into the
+// running best; an earlier pair wins ties on the value bits.
+__device__ __forceinline__ void pair_second(const floatx16& acc, uint32_t pk, int pair, uint32_t& bkey, int& bpair)
 {
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) pk[tt] = tile_min_key<0>(acc[tt]);
-}
-
-// Adds the second tile of pair `pair` (positions 16..31) and folds the pair
-// into the running best; an earlier pair wins ties on the value bits.
-template <int TT>
-__device__ __forceinline__ void pair_second(const floatx16 (&acc)[TT], const uint32_t (&pk)[TT], int pair,
-                                            uint32_t (&bkey)[TT], int (&bpair)[TT])
-{
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        const uint32_t k = min(pk[tt], tile_min_key<16>(acc[tt]));
-        if ((k & ~31u) < (bkey[tt] & ~31u)) {
-            bkey[tt] = k;
-            bpair[tt] = pair;
-        }
+    const uint32_t k = min(pk, tile_min_key<16>(acc));
+    if ((k & ~31u) < (bkey & ~31u)) {
+        bkey = k;
+        bpair = pair;
     }
 }
 
@@ -320,48 +299,34 @@ __device__ __forceinline__ void interleave_hint()
 // One stage's scores over all nct (even) codeword tiles, software-pipelined:
 // the fragments of tile ct+2 load and the MFMAs of tile ct+1 run while the
 // argmin of tile ct executes on the VALU.  Tiles 2p and 2p+1 form pair p.
-template <int D, int TT, bool TWO>
-__device__ __forceinline__ void stage_scan(const uint8_t* buf, uint32_t fa, int nct,
-                                           const half8 (&bz)[TT], const half8 (&bA)[TT][Shape<D>::KS],
-                                           const half8 (&bB)[TT][Shape<D>::KS], uint32_t (&bkey)[TT],
-                                           int (&bpair)[TT])
+template <int D, bool TWO>
+__device__ __forceinline__ void stage_scan(const uint8_t* buf, uint32_t fa, int nct, const half8& bz,
+                                           const half8 (&bA)[Shape<D>::KS], const half8 (&bB)[Shape<D>::KS],
+                                           uint32_t& bkey, int& bpair)
 {
-    constexpr int NM = TT * (1 + Shape<D>::KS * (TWO ? 2 : 1));   // MFMAs per tile
-    constexpr int NV = TT * 26;                                 // VALU ops of one tile's argmin
-    constexpr int ND = Shape<D>::KS + 1;                          // LDS reads of one tile's fragments
+    constexpr int NM = 1 + Shape<D>::KS * (TWO ? 2 : 1);   // MFMAs per tile
+    constexpr int NV = 26;                                 // VALU ops of one tile's argmin
+    constexpr int ND = Shape<D>::KS + 1;                   // LDS reads of one tile's fragments
     Frag<D> f0, f1;
-    floatx16 acc0[TT], acc1[TT];
-    uint32_t pk[TT];
+    floatx16 acc0, acc1;
+    uint32_t pk;
     load_frag<D>(f0, buf, fa, 0);
     load_frag<D>(f1, buf, fa, 1);
-    issue_tile<D, TT, TWO>(f0, bz, bA, bB, acc0);
+    issue_tile<D, TWO>(f0, bz, bA, bB, acc0);
     int ct = 0;
     for (; ct + 2 < nct; ct += 2) {
-        issue_tile<D, TT, TWO>(f1, bz, bA, bB, acc1);
+        issue_tile<D, TWO>(f1, bz, bA, bB, acc1);
         load_frag<D>(f0, buf, fa, ct + 2);
-        pair_first<TT>(acc0, pk);
+        pk = tile_min_key<0>(acc0);
         interleave_hint<NM, NV, ND, 1>();
-        issue_tile<D, TT, TWO>(f0, bz, bA, bB, acc0);
+        issue_tile<D, TWO>(f0, bz, bA, bB, acc0);
         load_frag<D>(f1, buf, fa, min(ct + 3, nct - 1));
-        pair_second<TT>(acc1, pk, ct >> 1, bkey, bpair);
+        pair_second(acc1, pk, ct >> 1, bkey, bpair);
         interleave_hint<NM, NV, ND, 1>();
     }
-    issue_tile<D, TT, TWO>(f1, bz, bA, bB, acc1);
-    pair_first<TT>(acc0, pk);
-    pair_second<TT>(acc1, pk, ct >> 1, bkey, bpair);
-}
-
-// The same for one token tile.
-template <int D, bool TWO>
-__device__ __forceinline__ void issue_one(const Frag<D>& f, const half8& bz, const half8 (&bA)[Shape<D>::KS],
-                                          const half8 (&bB)[Shape<D>::KS], floatx16& acc)
-{
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.bias, bz, (floatx16)0.0f, 0, 0, 0);
-#pragma unroll
-    for (int ks = 0; ks < Shape<D>::KS; ++ks) {
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.a[ks], bA[ks], acc, 0, 0, 0);
-        if (TWO) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.a[ks], bB[ks], acc, 0, 0, 0);
-    }
+    issue_tile<D, TWO>(f1, bz, bA, bB, acc1);
+    pk = tile_min_key<0>(acc0);
+    pair_second(acc1, pk, ct >> 1, bkey, bpair);
 }
 
 // One stage's scores for two token tiles with one fragment buffer and one
@@ -381,15 +346,11 @@ __device__ __forceinline__ void stage_scan_two(const uint8_t* buf, uint32_t fa, 
     Frag<D> f;
     floatx16 a0, a1;
     uint32_t pk[2];
-    auto issue0 = [&] { issue_one<D, TWO>(f, bz[0], bA[0], bB[0], a0); };
-    auto issue1 = [&] { issue_one<D, TWO>(f, bz[1], bA[1], bB[1], a1); };
+    auto issue0 = [&] { issue_tile<D, TWO>(f, bz[0], bA[0], bB[0], a0); };
+    auto issue1 = [&] { issue_tile<D, TWO>(f, bz[1], bA[1], bB[1], a1); };
     auto first = [&](int tt, const floatx16& a) { pk[tt] = tile_min_key<0>(a); };
     auto second = [&](int tt, const floatx16& a, int pair) {
-        const uint32_t k = min(pk[tt], tile_min_key<16>(a));
-        if ((k & ~31u) < (bkey[tt] & ~31u)) {
-            bkey[tt] = k;
-            bpair[tt] = pair;
-        }
+        pair_second(a, pk[tt], pair, bkey[tt], bpair[tt]);
     };
     load_frag<D>(f, buf, fa, 0);
     issue0();
@@ -602,8 +563,9 @@ __global__ __launch_bounds__((Cfg<D, WIDE>::THREADS), (Cfg<D, WIDE>::BLOCKS)) vo
         // One stage: TWO (stages 1..) scans with two passes per tile.  Stage 0 is
         // issued on its own, ahead of the loop over the later stages: with one
         // loop body holding both scan forms the register allocator kept both
-        // forms' values live across the loop and spilled (d = 128, three stages:
-        // 256 VGPRs and 32 bytes of scratch per lane, against 188 and none).
+        // forms' values live across the loop and spilled (d = 128, three stages,
+        // wide shape: 256 VGPRs and 32 bytes of scratch per lane, against 188 and
+        // none; the narrow shape holds 256 and 16-24 bytes, outside its scan).
         auto stage = [&](const int st, auto two_c) {
             constexpr bool TWO = decltype(two_c)::value;
             if (PERS && st + 1 == NS && item + 1 < it1) {
@@ -635,7 +597,7 @@ __global__ __launch_bounds__((Cfg<D, WIDE>::THREADS), (Cfg<D, WIDE>::BLOCKS)) vo
                 if constexpr (TT == 2)
                     stage_scan_two<D, TWO>(buf, fa, nct, bz, bA, bB, bkey, bpair);
                 else
-                    stage_scan<D, TT, TWO>(buf, fa, nct, bz, bA, bB, bkey, bpair);
+                    stage_scan<D, TWO>(buf, fa, nct, bz[0], bA[0], bB[0], bkey[0], bpair[0]);
 #pragma unroll
                 for (int tt = 0; tt < TT; ++tt) {
                     const int li = (int)(bkey[tt] & 31u);
@@ -777,19 +739,18 @@ constexpr int kSmallMaxItems = 8;   // token items per block (bounds the symbol 
 // One stage over the two codeword tiles of a small book with a single
 // fragment buffer.
 template <int D, bool TWO>
-__device__ __forceinline__ void stage_scan_small(const uint8_t* buf, uint32_t fa, const half8 (&bz)[1],
-                                                 const half8 (&bA)[1][Shape<D>::KS], const half8 (&bB)[1][Shape<D>::KS],
-                                                 uint32_t (&bkey)[1], int (&bpair)[1])
+__device__ __forceinline__ void stage_scan_small(const uint8_t* buf, uint32_t fa, const half8& bz,
+                                                 const half8 (&bA)[Shape<D>::KS], const half8 (&bB)[Shape<D>::KS],
+                                                 uint32_t& bkey, int& bpair)
 {
     Frag<D> f;
-    floatx16 acc0[1], acc1[1];
-    uint32_t pk[1];
+    floatx16 acc0, acc1;
     load_frag<D>(f, buf, fa, 0);
-    issue_tile<D, 1, TWO>(f, bz, bA, bB, acc0);
+    issue_tile<D, TWO>(f, bz, bA, bB, acc0);
     load_frag<D>(f, buf, fa, 1);
-    issue_tile<D, 1, TWO>(f, bz, bA, bB, acc1);
-    pair_first<1>(acc0, pk);
-    pair_second<1>(acc1, pk, 0, bkey, bpair);
+    issue_tile<D, TWO>(f, bz, bA, bB, acc1);
+    const uint32_t pk = tile_min_key<0>(acc0);
+    pair_second(acc1, pk, 0, bkey, bpair);
 }
 
 // A block barrier that orders LDS only: each wave's LDS operations complete
@@ -895,7 +856,7 @@ __global__ __launch_bounds__((Cfg<D, false>::THREADS), kSmallBlocks) void rvq_sm
             const uint8_t* buf = lds + st * buf_bytes;
             uint32_t bkey[1] = {0xFFFFFFFFu};
             int bpair[1] = {0};
-            stage_scan_small<D, TWO>(buf, fa, bz, cur, bB, bkey, bpair);
+            stage_scan_small<D, TWO>(buf, fa, bz[0], cur[0], bB[0], bkey[0], bpair[0]);
             const int li = (int)(bkey[0] & 31u);
             int cw = (li >> 4) * 32 + 8 * ((li & 15) >> 2) + 4 * hh + (li & 3);
             cw = min(cw, K - 1);  // only reachable with all-NaN scores; keeps reads in bounds
@@ -985,10 +946,13 @@ __global__ __launch_bounds__((Cfg<D, false>::THREADS), kSmallBlocks) void rvq_sm
 // fit a compute unit, so their loads and scans overlap; the staged form runs
 // one block per compute unit, which waits on three 64 KB copies for the scan of
 // a single wave.  512 books of 3 x 256 x 128, four tokens each: 36.0 -> 21.4 us
-// (2.8 -> 4.7 TB/s of books); 576 of 4 x 256 x 64: 39.5 -> 23 us.  What bounds it
-// now is the L1 rate of the fragment loads (32-byte pieces of 32 rows per
-// instruction).  Slower: the next stage's fragments in registers too (spills, or
-// one block per compute unit: 29-60 us), its lines touched ahead (34 us).
+// (2.8 -> 4.7 TB/s of books); 576 of 4 x 256 x 64: 39.5 -> 23 us.  Counters of the
+// first case: vector ALU 42% busy, matrix cores 13%, LDS 13%, the L1 0.6 tag
+// lookups per busy cycle (32-byte pieces of 32 rows per load), a quarter of the
+// waves' cycles waiting; a stage's loads are issued only after the compare of the
+// stage before.  The grouped instances keep 12-40 bytes of scratch at d <= 64 and
+// 24 at d = 128.  Slower: the next stage's fragments in registers too (more scratch,
+// or one block per compute unit: 29-60 us), its lines touched ahead (34 us).
 // Scores, keys, biases and residual splits are rvq_assign_kernel's, operation
 // for operation, and the winner is the lowest (score key, codeword) there too.
 constexpr int kFewTokens = 32;
@@ -996,8 +960,8 @@ constexpr int kFewTokens = 32;
 template <int D>
 struct FewLds {
     static constexpr int PITCH = (D / 8 + 1) * 16;   // bytes per token row: odd number of 16-byte chunks
-    half8 pad_;                                      // (alignment)
-    uint8_t hi[kFewTokens * PITCH], lo[kFewTokens * PITCH], chosen[kFewTokens * PITCH];
+    alignas(16) uint8_t hi[kFewTokens * PITCH];
+    uint8_t lo[kFewTokens * PITCH], chosen[kFewTokens * PITCH];
     uint64_t best[8][kFewTokens];                    // each wave's best (score key, codeword) per token
 };
 
@@ -1009,7 +973,7 @@ __global__ __launch_bounds__(512, D <= 64 ? 6 : D <= 128 ? 4 : 2) void rvq_few_k
     int64_t n_streams, int64_t n_items)
 {
     constexpr int KS = D / 16, NCH = D / 8, PITCH = FewLds<D>::PITCH;
-        __shared__ FewLds<D> l;
+    __shared__ FewLds<D> l;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, hh = lane >> 5, n_waves = blockDim.x >> 6;
     const int nt = (int)(GRP ? G * Ta : Ta);   // <= kFewTokens
@@ -1476,12 +1440,15 @@ int rvq_dispatch(const fkv_rvq_desc* desc, int ns, const uint16_t* x_f16, const 
 }
 
 // From this many head vectors per call on, fkv_rvq_assign_encode runs the
-// assignment and then the span encode as two kernels.  The fused kernel's
-// encode tail sits on every block's critical path (one block per compute unit
-// at d = 128, so about 1,000 blocks in a row per compute unit at the
-// long-context shape: 0.85 ms more than the separate encode's 0.12 ms);
-// below a few thousand blocks the one launch and the symbols never read back
-// win (GPT-2 shape: 37 us fused against 41 us).
+// assignment and then the span encode as two kernels.  Small calls gain from the
+// one launch and the symbols never read back (GPT-2 shape: 37 us fused against 41
+// us); in large ones the encode's tail and its LDS cost the fused kernel more than
+// the separate encode takes, by little since two or three blocks share a compute
+// unit.  Fused and separate (us), K = 256: d = 128, S = 3, 2.0 M vectors 624 and 601, 7.7
+// M 2270 and 2220, 16.8 M 4934 and 4803; d = 64, S = 2, 2.0 M 216 and 208, 16.8 M 1722 and
+// 1663; S = 4, 9.2 M 1968 and 1948.  Small books are 2% faster fused at every size
+// (K = 64, 16.8 M 617 and 627), and d = 256 is from 4 M on (9.2 M 7380 and 8416: the
+// separate assignment keeps more scratch).
 constexpr int64_t kSplitHeadVectors = (int64_t)1 << 23;
 
 bool encode_split(const fkv_rvq_desc* desc, const uint8_t* symbols)

@@ -386,3 +386,15 @@ def test_book_groups_host_helper(F):
     with pytest.raises(ValueError):
         F.book_groups(np.array([0, 0, 1], np.int32))
     assert F.book_groups(np.zeros(0, np.int32)).shape[0] == 0
+
+
+def test_stream_handle_of_the_binding(F, monkeypatch):
+    """The current stream's handle through torch's raw getter, and through a Stream object where a torch has no
+    such getter; a handle that the caller gives is taken as it is."""
+    from types import SimpleNamespace
+    cuda = SimpleNamespace(current_device=lambda: 3, current_stream=lambda: SimpleNamespace(cuda_stream=77))
+    raw = SimpleNamespace(_cuda_getCurrentRawStream=lambda device: 100 + device)
+    monkeypatch.setattr(F, "_TORCH", SimpleNamespace(_C=raw, cuda=cuda))
+    assert F._stream(None) == 103 and F._stream(5) == 5 and F._stream(0) == 0
+    monkeypatch.setattr(F, "_TORCH", SimpleNamespace(_C=SimpleNamespace(), cuda=cuda))
+    assert F._stream(None) == 77
