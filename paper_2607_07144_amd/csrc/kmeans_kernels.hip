@@ -475,21 +475,27 @@ extern "C" int fkv_kmeans_accumulate(const fkv_rvq_desc* desc, const uint16_t* x
         return FKV_ERR_INVALID_ARG;
     const int n_slices = (D.d + kSlice - 1) / kSlice;
     if (Ta * (std::min(kSlice, (int)D.d) / 8) > 0x7fffffff - kAccThreads * kAccBatch) return FKV_ERR_UNSUPPORTED;
-    // The sort costs a chunk about 5 us of barriers, which few tokens do not repay,
-    // and the direct form pays 1.3 us per stream of a book.  A narrow row takes few
-    // lanes, so the atomics it saves are few, and two direct blocks fit a compute
-    // unit.  Measured, direct and sorted (us): one stream per book, K = 256: d = 64,
-    // 16 tokens 12.2 and 17.1, 300 tokens 25.5 and 30.0, 2500 tokens 68.1 and 58.3;
-    // d = 8, 4000 tokens 19.4 and 31.0; d = 48, 20,000 tokens in two streams 273 and
-    // 321.  200 books of 64 x 256: 4 streams of 64 tokens 18.7 and 19.0, 32 streams
-    // of 64 tokens 71.8 and 55.5.
-    const bool few = D.n_streams < 4 * (int64_t)D.n_books, narrow = D.d <= 24 || (D.d < 56 && D.n_books > 256);
-    const bool sort = narrow ? !few && Ta < 1024
-                             : !few || D.n_streams * Ta >= (int64_t)D.n_books * std::max(900, 8 * (int)D.K);
     auto lds_bytes = [](int K, int dc, bool sort) {
         return (size_t)K * (dc + 1) * 8 + (size_t)K * 4 + (kAccThreads + 1) * 4 + (sort ? (256 + 4) * 4 + kChunk * 2 : 0);
     };
-    const size_t shm = lds_bytes(D.K, std::min(kSlice, (int)D.d), sort);
+    const int dc = std::min(kSlice, (int)D.d);
+    // The sort costs a chunk about 5 us of barriers, which few tokens do not repay,
+    // and the direct form pays 1.3 us per stream of a book.  A narrow row takes few
+    // lanes, so the atomics it saves are few, and two direct blocks fit a compute
+    // unit; at stage 0, whose registers allow it too, so they do for up to 150
+    // codewords.  Measured, direct and sorted (us): one stream per book, K = 256: d = 64,
+    // 16 tokens 12.2 and 17.1, 300 tokens 25.5 and 30.0, 2500 tokens 68.1 and 58.3;
+    // d = 8, 4000 tokens 19.4 and 31.0; d = 48, 20,000 tokens in two streams 273 and
+    // 321.  200 books of 64 x 256: 4 streams of 64 tokens 18.7 and 19.0, 32 streams
+    // of 64 tokens 71.8 and 55.5.  Stage 0, 288 books of 64 x 128: 950 tokens 26.5 and 31.0,
+    // 2500 52.3 and 46.5; of 256 x 100 (1152 blocks): 2500 122 and 142, 4000 183 and 195.
+    const bool few = D.n_streams < 4 * (int64_t)D.n_books, narrow = D.d <= 24 || (D.d < 56 && D.n_books > 256);
+    const int64_t blocks = (int64_t)D.n_books * n_slices;
+    const bool pairs = stage == 0 && blocks > 256 && 2 * lds_bytes(D.K, dc, false) <= 160 * 1024;
+    const int paired = (1000 + 10 * (int)D.K) * (blocks > 1024 || dc < kSlice ? 2 : 1);
+    const int64_t repays = std::max(pairs ? paired : 900, 8 * (int)D.K);
+    const bool sort = narrow ? !few && Ta < 1024 : !few || D.n_streams * Ta >= D.n_books * repays;
+    const size_t shm = lds_bytes(D.K, dc, sort);
     static std::once_flag once[12];   // one per kernel instance below
     auto go = [&](int slot, auto kern) {
         std::call_once(once[slot], [&] {

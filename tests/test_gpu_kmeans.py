@@ -84,6 +84,7 @@ def test_sorted_sums_match_oracle(fkv, orc, ns, T, d, S, K, stage, nb, extreme):
 
 @pytest.mark.parametrize("d,S,K,stage", [
     (64, 2, 256, 1), (128, 3, 200, 2), (8, 1, 256, 0), (24, 8, 31, 7), (72, 5, 256, 4), (256, 4, 129, 3), (48, 6, 256, 5),
+    (64, 1, 100, 0), (136, 2, 128, 0),
 ])
 def test_direct_and_sorted_forms_agree(fkv, d, S, K, stage):
     """The same 1500 tokens of each book as one stream (fewer tokens than the sort repays, or a narrow row: added
