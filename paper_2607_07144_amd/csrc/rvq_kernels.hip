@@ -1297,7 +1297,9 @@ bool two_wide(const fkv_rvq_desc* dsc)
 // 13.6, 8 tokens 7.9 and 8.5, K = 256, 32 tokens 18.6 and 15.6; d = 128, S = 4, K = 32,
 // 300 items of 32 20.0 and 28.2; d = 192, S = 4, K = 32, 1500 of 32 86 and 117; d = 16,
 // S = 4, K = 32, 600 of 32 8.5 and 12.3.  One stage of a large book has no second load
-// to overlap either: d = 192, S = 1, K = 192, 300 items 10.4 and 12.7.
+// to overlap either: d = 192, S = 1, K = 192, 300 items 10.4 and 12.7.  Books of 129 to
+// 192 codewords give it six waves where the staged form has eight: d = 16, S = 3,
+// 1500 groups of 32 16.8 and 21.1; d = 144, S = 2, 300 of 32 18.1 and 21.0.
 template <int D>
 bool few_tokens(const fkv_rvq_desc* dsc, int ns, const GroupArgs& grp)
 {
@@ -1317,7 +1319,10 @@ bool few_tokens(const fkv_rvq_desc* dsc, int ns, const GroupArgs& grp)
     if (D <= 64 && ns >= 3 && tokens > 8 && K <= 64 && n_items <= 1024) return false;
     if (D <= 208 && ns == 2 && tokens > 16 && K <= 64 && n_items <= 512) return false;
     if (D > 128 && D <= 208 && ns >= 3 && tokens > 16 && K <= 32) return false;
-    return !(ns == 1 && K > 128 && (D <= 64 ? n_items <= 512 : D > 128 && D <= 208 && (n_items <= 512 || tokens >= 16)));
+    if (D <= 208 && tokens > 16 && K > 128 && K <= 192 && (D <= 32 || (D > 128 && (ns <= 2 || n_items <= 512)))) return false;
+    if (ns > 1 || K <= 128) return true;
+    if (D <= 64) return n_items > 512;
+    return D <= 128 || !(D <= 208 ? n_items <= 512 || tokens >= 16 : n_items <= 1024 && tokens >= 16);
 }
 
 // Whether the staged form's blocks are narrow (d <= 128): with more than one full

@@ -330,6 +330,7 @@ def test_few_tokens_more_items_than_blocks(fkv):
     (16, 3, 100, 1, 32, 600), (16, 3, 64, 3, 4, 100), (64, 3, 64, 4, 4, 100), (64, 1, 192, 2, 1, 300), (64, 4, 33, 2, 5, 600),
     (80, 3, 192, 3, 6, 300), (80, 3, 64, 4, 2, 300), (80, 2, 100, 2, 16, 400), (96, 2, 64, 1, 32, 300), (128, 4, 40, 2, 16, 300),
     (192, 1, 200, 4, 8, 300), (192, 3, 32, 1, 30, 300), (208, 2, 64, 2, 15, 280), (256, 3, 64, 1, 32, 300),
+    (16, 3, 192, 1, 20, 1100), (144, 2, 150, 2, 16, 300), (256, 1, 192, 4, 4, 300),
 ])
 def test_few_tokens_of_small_books(fkv, d, S, K, G, n, ng):
     """Calls of at most 32 tokens per group on both sides of the choice between the few-token kernel and the
